@@ -35,7 +35,7 @@ PHASE_OF = {
     "coarsen": ["match", "match_chunks", "hedge_keys", "coarsen_init", "decode", "attach", "lead",
                 "parent", "qbuild", "qbuild_block", "qbuild_huge", "dedup", "copy_pins", "classify",
                 "node_ids", "hedge_ids", "incidence", "radix_hist", "radix_scatter", "level_fixup"],
-    "refine": ["project", "side_weights", "gain_nodes", "gain_hedges", "gain_stats", "gain_update",
+    "refine": ["project", "side_weights", "gain_nodes", "gain_hedges", "gain_lds", "gain_reduce", "gain_stats", "gain_update",
                "select", "select_pick", "seg_select", "seg_balance", "seg_initial", "balance", "flip",
                "round", "level_bound"],
 }

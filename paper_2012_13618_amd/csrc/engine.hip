@@ -335,11 +335,27 @@ void run_match_keys(Ctx &cx, Level &L, const uint8_t *sact, uint64_t *key, const
 
 // Gains of the segments in sg.gmask: two launches.  With stats, the node pass
 // also fills the per-list counts / gain extremes used by the selection.
-void run_gains(Ctx &cx, Level &L, Segs &sg, int32_t *gain, bool stats, const int32_t *go)
+void run_gains(Ctx &cx, Level &L, Segs &sg, int32_t *gain, bool stats, const int32_t *go, bool need_cc)
 {
     LaunchCtx &lc = cx.lc;
     check_lists(L);
     cx.pins_refined += L.P;
+    if (L.gs.rec) {
+        GainLdsArgs a{L.gs, L.S, L.off, L.pins, L.hw, L.nbase, sg.gmask, L.side, need_cc ? (void *)L.cc : nullptr,
+                      L.cc_pk, go};
+        double sums = 4.0 * L.N + 4.0 * L.maxseg_nodes * (L.gs.bound - L.S);
+        double b = 8.0 * L.E + 4.0 * L.P + 1.0 * L.N + (need_cc ? (L.cc_pk ? 4.0 : 8.0) * L.E : 0.0) + sums;
+        if (L.maxseg_nodes <= kGlNodesHalf)
+            launch(lc, "gain_lds", b, k_gain_lds<kGlNodesHalf>, L.gs.bound, kGlThreads, 0, a);
+        else
+            launch(lc, "gain_lds", b, k_gain_lds<kGlNodes>, L.gs.bound, kGlThreads, 0, a);
+        int32_t per = stats ? 64 : 32;
+        launch(lc, "gain_reduce", sums + 8.0 * L.N, k_gain_reduce, ceil_div(L.N, per), kBlock, 0, L.N, per, L.gs,
+               (const int32_t *)L.nseg, (const int32_t *)L.nbase, (const uint8_t *)sg.gmask,
+               (const uint8_t *)L.side, gain, (const uint8_t *)sg.mode, stats ? sg.st.tot : nullptr, sg.st.gmax,
+               sg.st.gmin, go);
+        return;
+    }
     int64_t hv = std::max<int64_t>(ceil_div(L.E, kBlock) + ceil_div(L.nmid, kBlock / 64) + L.nbig,
                                    ceil_div(L.nbig_bound, kBlock));
     double cb = L.cc_pk ? 4.0 : 8.0;  // bytes of one contribution pair
@@ -359,6 +375,45 @@ void run_gains(Ctx &cx, Level &L, Segs &sg, int32_t *gain, bool stats, const int
            stats ? sg.st.tot : nullptr, sg.st.gmax, sg.st.gmin, go, (const int32_t *)L.chunk_node,
            (const int32_t *)L.chunk_beg, (const int32_t *)L.chunk_big, (const int32_t *)L.big_chunks,
            L.big_done, L.S, nw);
+}
+
+// The slab tables of the levels that compute their gains in LDS (one launch);
+// the levels share one buffer of partial sums.
+static void build_gain_slabs(Ctx &cx, Level *lv, int32_t n)
+{
+    Arena &ar = *cx.ar;
+    GlTableArgs ta{};
+    int32_t q = 0;
+    int64_t parts = 0;
+    std::vector<Level *> on;
+    auto flush = [&]() {
+        if (q == 0) return;
+        launch3(cx.lc, "gain_slabs", 0.0, k_gain_slabs, dim3(1, (unsigned)q, 1), 1024, 0, ta);
+        q = 0;
+    };
+    for (int32_t j = 0; j < n; j++) {
+        Level &L = lv[j];
+        if (!gl_ok(L)) continue;
+        GainSlabs &gs = L.gs;
+        gs.pps = (int32_t)ceil_div(L.P, gl_slabs(L));
+        gs.bound = L.S + (int32_t)ceil_div(L.P, gs.pps);
+        gs.rec = ar.get<int4>(gs.bound);
+        gs.slab0 = ar.get<int32_t>((int64_t)L.S + 1);
+        gs.pbase = ar.get<int64_t>(L.S);
+        // sum over the segments of (1 + pins / pps) times their nodes
+        parts = std::max(parts, (int64_t)L.N + ceil_div(L.P, gs.pps) * L.maxseg_nodes);
+        on.push_back(&L);
+        ta.off[q] = L.off;
+        ta.nbase[q] = L.nbase;
+        ta.hbase[q] = L.hbase;
+        ta.gs[q] = gs;
+        ta.S = L.S;
+        if (++q == kBoundLevels) flush();
+    }
+    flush();
+    if (on.empty()) return;
+    int32_t *part = ar.get<int32_t>(parts);
+    for (Level *L : on) L->gs.part = part;
 }
 
 static int id_bits(const Level &L)
@@ -707,7 +762,7 @@ static int64_t refine_level(Ctx &cx, Level &L, Segs &sg, int32_t j, int32_t *gai
         bool seg = seg_path(cx, L, 1);
         if (ri == 0 || !incr) {
             launch(lc, "round", 0.0, k_round_balance, gs, kBlock, 0, rb, sg.st, sg.go, ri);
-            run_gains(cx, L, sg, gain, !seg && !chunk, gc);
+            run_gains(cx, L, sg, gain, !seg && !chunk, gc, incr);
         } else {
             // the round's test and the marking of the last round's moves: one launch
             launch(lc, "round", 0.0, k_round_balance_log, gs + lg, kBlock, 0, gs, rb, sg.st, sg.go, ri,
@@ -832,6 +887,8 @@ void bisect_all(Ctx &cx, Level &L0, Segs &sg, int32_t active0)
             lv[j].cc_pk = hb[2 * j + 1] < 32768;
         }
     }
+
+    build_gain_slabs(cx, lv.data(), Lmax + 1);
 
     // balance candidate buffers sized for the largest segment
     int32_t maxn = 1;
@@ -2095,6 +2152,7 @@ static Level step_level(Ctx &cx, const bp_hypergraph *hg)
     L.maxseg_pins = L.P;
     L.maxseg_hedges = L.E;
     build_incidence(cx, L);
+    build_gain_slabs(cx, &L, 1);
     return L;
 }
 

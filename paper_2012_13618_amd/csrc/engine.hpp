@@ -2,6 +2,7 @@
 #pragma once
 #include "batch.hpp"
 #include "coarsen.hpp"
+#include "gain_lds.hpp"
 #include "kway.hpp"
 #include "refine.hpp"
 #include "uncoarsen.hpp"
@@ -291,7 +292,8 @@ void build_incidence(Ctx &cx, Level &L);
 // hkey: the level's hyperedge keys when already computed, else null
 void run_match_keys(Ctx &cx, Level &L, const uint8_t *sact, uint64_t *key, const uint64_t *hkey = nullptr);
 void bisect_all(Ctx &cx, Level &L0, Segs &sg, int32_t active0);
-void run_gains(Ctx &cx, Level &L, Segs &sg, int32_t *gain, bool stats, const int32_t *go);
+// need_cc: the hyperedges' contributions are wanted as well (incremental rounds)
+void run_gains(Ctx &cx, Level &L, Segs &sg, int32_t *gain, bool stats, const int32_t *go, bool need_cc = false);
 void run_select(Ctx &cx, Level &L, Segs &sg, const int32_t *gain, const int32_t *go, int32_t clip = 0);
 
 }  // namespace bp

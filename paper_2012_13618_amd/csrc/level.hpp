@@ -11,6 +11,18 @@
 
 namespace bp {
 
+// Slabs of a level's hyperedges for the gains in LDS (gain_lds.hpp): slab i is
+// hyperedges [rec.y, rec.z) of segment rec.x, the segment's rec.w-th; segment s
+// owns slabs [slab0[s], slab0[s + 1]) and the partial sums from part + pbase[s].
+struct GainSlabs {
+    int4 *rec = nullptr;       // null: the level's gains do not go through LDS
+    int32_t *slab0 = nullptr;  // [S + 1]
+    int64_t *pbase = nullptr;  // [S]
+    int32_t *part = nullptr;
+    int32_t pps = 0;           // pins a slab
+    int32_t bound = 0;         // slabs at most
+};
+
 struct Level {
     int32_t N = 0, E = 0, P = 0, S = 0;
     int32_t *off = nullptr;   // [E+1]
@@ -46,6 +58,7 @@ struct Level {
     int32_t span_bits = 32;
     int2 *cc = nullptr;         // [E] per-hyperedge gain contributions (scratch)
     int32_t cc_pk = 0;          // contributions packed as two int16 (every w(e) < 2^15)
+    GainSlabs gs;
 };
 
 // Sizes and counters read back once per level.

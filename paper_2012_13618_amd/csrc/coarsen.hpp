@@ -20,6 +20,7 @@
 #pragma once
 #include "level.hpp"
 #include "scan.hpp"
+#include "transpose.hpp"
 
 namespace bp {
 
@@ -38,7 +39,8 @@ struct CoarsenBufs {
     int32_t *hslot;    // [E]
     int32_t *rep;      // [E]
     int32_t *wsum;     // [E]
-    int32_t *hdst;     // [E]
+    int32_t *csrc;     // [E] first pin in qpins of each coarse hyperedge
+    uint32_t *counts;  // the coarse pins' tile histograms (first digit)
     int32_t *hb_tmp;   // [S]
     uint64_t *tkeys;   // [T]
     int32_t *tmin;     // [T]
@@ -670,23 +672,50 @@ __global__ __launch_bounds__(kBlock) void k_dd_resolve(int32_t E, const int32_t 
 }
 
 
-struct CopyPinsOp {
-    const int32_t *off, *rep, *qlen, *qpins, *hdst;
+// The coarse level's pins from the fine hyperedges' lists, tile t of kRsTile
+// coarse pins a workgroup: coarse hyperedge e's pins start at csrc[e] of qpins.
+// The tile's histogram of the pins' low digit - the first of the incidence
+// sort that follows - is taken on the way.  Sizes come from the device (totEP),
+// the grid is a bound.  Bound by memory, 8 bytes a pin; one thread copying
+// each short hyperedge ran at 0.55 TB/s (103 M pins over 8.0 M hyperedges:
+// 1.9 ms; now 0.36).
+struct CopyPins {
+    const uint64_t *totEP;
+    const int32_t *coff, *csrc, *tfirst, *qpins;
     int32_t *cpins;
-    template <int S> __device__ __forceinline__ void run(int64_t vb, int32_t count, const int32_t *list) const;
+    uint32_t *counts;
 };
 
-template <int S>
-__device__ __forceinline__ void CopyPinsOp::run(int64_t vb, int32_t count, const int32_t *list) const
+__device__ __forceinline__ void copy_pins_tile(int64_t t, const CopyPins &c)
 {
-    int lane, stride;
-    int32_t e = sched_hedge_at<S>(vb, count, list, lane, stride);
-    if (e < 0) return;
-    int32_t b = off[e];
-    if (!thread_split<S>(off[e + 1] - b)) return;
-    if (rep[e] != e) return;
-    int32_t len = qlen[e], dst = hdst[e];
-    for (int i = lane; i < len; i += stride) cpins[dst + i] = qpins[b + i];
+    __shared__ int32_t delta[kRsTile];
+    __shared__ TileLds tl;
+    __shared__ uint32_t h[256];
+    const int32_t E = (int32_t)(*c.totEP >> 32);
+    const int64_t P = (int64_t)(*c.totEP & 0xffffffffu), tile = t * kRsTile;
+    if (tile >= P) return;
+    const int64_t ntiles = ceil_div(P, kRsTile);
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    h[threadIdx.x] = 0;
+    const int32_t *coff = c.coff, *csrc = c.csrc;
+    const int32_t d0 = tile_map<false>(t, ntiles, E, coff, c.tfirst, delta, tl,
+                                       [=](int32_t e) { return csrc[e] - coff[e]; });
+    int32_t x[kRsItems];
+#pragma unroll
+    for (int r = 0; r < kRsItems; r++) {
+        const int word = w * kRsItems + r;
+        const int64_t i = tile + word * 64 + lane;
+        x[r] = i < P ? c.qpins[i + tile_val(word, lane, delta, tl, d0)] : 0;
+    }
+#pragma unroll
+    for (int r = 0; r < kRsItems; r++) {
+        const int64_t i = tile + (w * kRsItems + r) * 64 + lane;
+        if (i >= P) continue;
+        c.cpins[i] = x[r];
+        atomicAdd(&h[x[r] & 255], 1u);
+    }
+    __syncthreads();
+    c.counts[(int64_t)threadIdx.x * ntiles + t] = h[threadIdx.x];
 }
 
 // Sizes of the coarse level, its segment tables and which segments continue.

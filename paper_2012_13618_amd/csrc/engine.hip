@@ -40,24 +40,15 @@ static void set_schedule(const Schedule &s)
 // ---- one coarsening step ------------------------------------------------------
 
 // The coarse level's hyperedge lists by degree (blocks [0, ncls)) and the copy
-// of its pins (the other blocks, by degree bucket of the fine hyperedges), in
-// one launch: their outputs are disjoint.
+// of its pins (the other blocks, a tile each), in one launch: their outputs
+// are disjoint.
 __global__ __launch_bounds__(kBlock) void k_classify_copy(int64_t ncls, int32_t E, const int32_t *coff,
                                                           const uint64_t *tot, int32_t *lmid, int32_t *lbig,
-                                                          int32_t *lhuge, int32_t *counters, CopyPinsOp op,
-                                                          int32_t nmid, const int32_t *flmid, int32_t nbig,
-                                                          const int32_t *flbig)
+                                                          int32_t *lhuge, int32_t *counters, CopyPins cp)
 {
     int64_t b = blockIdx.x;
-    if (b < ncls) {
-        classify_block(b, E, coff, tot, lmid, lbig, lhuge, counters);
-        return;
-    }
-    b -= ncls;
-    int64_t ns = ceil_div(E, kBlock), nw = ceil_div(nmid, kBlock / 64);
-    if (b < ns) op.template run<SMALL>(b, E, nullptr);
-    else if (b < ns + nw) op.template run<WAVE>(b - ns, nmid, flmid);
-    else op.template run<BLOCK>(b - ns - nw, nbig, flbig);
+    if (b < ncls) classify_block(b, E, coff, tot, lmid, lbig, lhuge, counters);
+    else copy_pins_tile(b - ncls, cp);
 }
 
 void coarsen_level(Ctx &cx, Level &f, Segs &sg, uint8_t *&sact, uint8_t *&sact_next, int32_t l,
@@ -81,7 +72,9 @@ void coarsen_level(Ctx &cx, Level &f, Segs &sg, uint8_t *&sact, uint8_t *&sact_n
     b.hslot = ar.get<int32_t>(E);
     b.rep = ar.get<int32_t>(E);
     b.wsum = ar.get<int32_t>(E);
-    b.hdst = ar.get<int32_t>(E);
+    const int64_t ptiles = ceil_div(P > 0 ? P : 1, kRsTile);
+    b.csrc = ar.get<int32_t>(E);
+    b.counts = ar.get<uint32_t>(256 * ptiles);
     b.hb_tmp = ar.get<int32_t>(S);
     int64_t T = 1024;
     while (T < 2 * (int64_t)E) T <<= 1;
@@ -103,6 +96,8 @@ void coarsen_level(Ctx &cx, Level &f, Segs &sg, uint8_t *&sact, uint8_t *&sact_n
     c.nbase = ar.get<int32_t>(S + 1);
     c.hbase = ar.get<int32_t>(S + 1);
     alloc_lists(ar, c, E);
+    c.tfirst = ar.get<int32_t>(ptiles);
+    c.counts0 = b.counts;
 
     int64_t initn = std::max<int64_t>(std::max<int64_t>(N, E), T);
     uint64_t *hkey = ar.get<uint64_t>(E);
@@ -178,7 +173,8 @@ void coarsen_level(Ctx &cx, Level &f, Segs &sg, uint8_t *&sact, uint8_t *&sact_n
     auto compact = [&]() {
         const int32_t *rep = b.rep, *qlen = b.qlen, *hseg = f.hseg, *hbase = f.hbase,
                       *wsum = b.wsum;
-        int32_t *coff = c.off, *chw = c.hw, *chseg = c.hseg, *hdst = b.hdst, *hbt = b.hb_tmp;
+        const int32_t *foff = f.off;
+        int32_t *coff = c.off, *chw = c.hw, *chseg = c.hseg, *csrc = b.csrc, *hbt = b.hb_tmp, *tfirst = c.tfirst;
         scan<uint64_t>(
             lc, ar, "hedge_ids", E,
             [=] __device__(int64_t e) -> uint64_t {
@@ -192,15 +188,16 @@ void coarsen_level(Ctx &cx, Level &f, Segs &sg, uint8_t *&sact, uint8_t *&sact_n
                     coff[id] = (int32_t)ex;
                     chw[id] = wsum[e];
                     chseg[id] = s;
-                    hdst[e] = (int32_t)ex;
+                    csrc[id] = foff[e];
+                    tile_starts(id, (int32_t)ex, (int32_t)(val & 0xffffffffu), tfirst);
                 }
             },
             b.totEP);
-        CopyPinsOp cop{(const int32_t *)f.off, rep, qlen, (const int32_t *)b.qpins, (const int32_t *)b.hdst, c.pins};
+        CopyPins cp{(const uint64_t *)b.totEP, (const int32_t *)c.off, (const int32_t *)b.csrc,
+                    (const int32_t *)c.tfirst, (const int32_t *)b.qpins, c.pins, b.counts};
         int64_t ncls = ceil_div(E, kClsItems);
-        launch(lc, "copy_pins", 4.0 * E + 8.0 * P, k_classify_copy, ncls + buckets_grid(E, f.nmid, f.nbig), kBlock, 0,
-               ncls, E, (const int32_t *)c.off, (const uint64_t *)b.totEP, c.lmid, c.lbig, c.lhuge, b.counters, cop,
-               f.nmid, (const int32_t *)f.lmid, f.nbig, (const int32_t *)f.lbig);
+        launch(lc, "copy_pins", 4.0 * E + 8.0 * P, k_classify_copy, ncls + ptiles, kBlock, 0, ncls, E,
+               (const int32_t *)c.off, (const uint64_t *)b.totEP, c.lmid, c.lbig, c.lhuge, b.counters, cp);
         launch(lc, "level_fixup", 0.0, k_level_fixup, 1, kFixupThreads, 0, S, N, E, (const int32_t *)f.nbase,
                (const int32_t *)f.hbase, (const int32_t *)b.cid, (const int32_t *)b.hb_tmp,
                (const int32_t *)b.totN, (const uint64_t *)b.totEP, l + 1, cx.prm.max_levels,
@@ -260,25 +257,31 @@ void build_incidence(Ctx &cx, Level &L)
     const int32_t N = L.N, E = L.E, P = L.P;
     uint32_t *k0 = ar.get<uint32_t>(P), *k1 = ar.get<uint32_t>(P);
     int32_t *v0 = ar.get<int32_t>(P), *v1 = ar.get<int32_t>(P);
-    ExpandPairsOp eop{(const int32_t *)L.off, v0};
-    launch(lc, "incidence", 4.0 * P, k_buckets<ExpandPairsOp>, buckets_grid(E, L.nmid, L.nbig), kBlock, 0, eop, E,
-           L.nmid, (const int32_t *)L.lmid, L.nbig, (const int32_t *)L.lbig);
     int bits = 0;
     while (bits < 31 && ((int64_t)1 << bits) < (int64_t)N) bits++;
     int64_t ntiles = ceil_div(P > 0 ? P : 1, kRsTile);
-    uint32_t *counts = ar.get<uint32_t>(256 * ntiles), *offs = ar.get<uint32_t>(256 * ntiles);
+    uint32_t *counts = L.counts0 ? L.counts0 : ar.get<uint32_t>(256 * ntiles), *offs = ar.get<uint32_t>(256 * ntiles);
     uint32_t *tot = ar.get<uint32_t>(1);
-    // the first pass reads the keys (the pins) in place
+    if (!L.tfirst && P > 0) {
+        L.tfirst = ar.get<int32_t>(ntiles);
+        launch(lc, "incidence", 4.0 * E, k_tile_starts, ceil_div(E, kBlock), kBlock, 0, E, (const int32_t *)L.off,
+               L.tfirst);
+    }
+    // the first pass reads the keys (the pins) in place and finds the values
+    // (their hyperedges) from off; it runs for a single node too
     const uint32_t *kin = (const uint32_t *)L.pins;
-    for (int shift = 0; shift < bits && P > 0; shift += 8) {
-        launch(lc, "radix_hist", 4.0 * P, k_rs_hist, ntiles, kBlock, 0, kin, (int64_t)P, shift, counts, ntiles);
+    for (int shift = 0; (shift == 0 || shift < bits) && P > 0; shift += 8) {
+        if (shift > 0 || !L.counts0)
+            launch(lc, "radix_hist", 4.0 * P, k_rs_hist, ntiles, kBlock, 0, kin, (int64_t)P, shift, counts, ntiles);
         const uint32_t *cnt = counts;
         uint32_t *of = offs;
         scan<uint32_t>(
             lc, ar, "radix_scan", 256 * ntiles, [=] __device__(int64_t i) -> uint32_t { return cnt[i]; },
             [=] __device__(int64_t i, uint32_t ex, uint32_t) { of[i] = ex; }, tot);
-        launch(lc, "radix_scatter", 16.0 * P, k_rs_scatter, ntiles, kBlock, 0, kin, (const int32_t *)v0,
-               (int64_t)P, shift, (const uint32_t *)offs, ntiles, k1, v1);
+        launch(lc, "radix_scatter", (shift == 0 ? 12.0 : 16.0) * P,
+               shift == 0 ? &k_rs_scatter<true> : &k_rs_scatter<false>, ntiles, kBlock, 0, E, (const int32_t *)L.off,
+               (const int32_t *)L.tfirst, kin, (const int32_t *)v0, (int64_t)P, shift, (const uint32_t *)offs, ntiles,
+               k1, v1);
         kin = k1;
         std::swap(k0, k1);
         std::swap(v0, v1);

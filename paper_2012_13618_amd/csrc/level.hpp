@@ -59,6 +59,8 @@ struct Level {
     int2 *cc = nullptr;         // [E] per-hyperedge gain contributions (scratch)
     int32_t cc_pk = 0;          // contributions packed as two int16 (every w(e) < 2^15)
     GainSlabs gs;
+    int32_t *tfirst = nullptr;   // hyperedge holding the first pin of each radix tile, once known
+    uint32_t *counts0 = nullptr; // the radix tiles' histograms of the first digit, once taken
 };
 
 // Sizes and counters read back once per level.

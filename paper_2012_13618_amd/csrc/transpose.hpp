@@ -4,7 +4,9 @@
 // Built by a stable LSD radix sort of (node id, hyperedge id) pairs taken in
 // pin order, 8-bit digits: per-tile digit histograms, one prefix scan of the
 // (digit, tile) counts, and a stable scatter whose in-tile ranks come from
-// wavefront ballots and which writes each tile out in digit order.  Node offsets are binary searches into the sorted keys.
+// wavefront ballots and which writes each tile out in digit order.  The first
+// pass finds each pin's hyperedge itself (tile_map).  Node offsets are binary
+// searches into the sorted keys.
 //
 // With it, the per-node steps - the 64-bit minimum of Algorithm 1 and the gain
 // sum of Algorithm 4 (uncoarsen.hpp) - are gathers over a node's own
@@ -39,14 +41,83 @@ __global__ __launch_bounds__(kBlock) void k_rs_hist(const uint32_t *keys, int64_
     counts[(int64_t)threadIdx.x * ntiles + blockIdx.x] = h[threadIdx.x];
 }
 
+// Which hyperedge each of a tile's kRsTile consecutive pins belongs to, by the
+// whole workgroup (kBlock threads): the hyperedges that start in the tile set a
+// bit at their first pin and leave val(e) there, and a pin looks up the last
+// set bit at or before it.  Every load is coalesced - off once per hyperedge -
+// where a thread walking each hyperedge writes one pin a lane from as many
+// lines.  tfirst[t] is the hyperedge that holds pin t * kRsTile; EMPTY: whether
+// hyperedges without pins may occur.
+struct TileLds {
+    unsigned long long bits[kRsTile / 64];
+    int32_t last[kRsTile / 64];  // the last start before each word, or -1
+};
+
+template <bool EMPTY, typename Val>
+__device__ __forceinline__ int32_t tile_map(int64_t t, int64_t ntiles, int32_t E, const int32_t *off,
+                                            const int32_t *tfirst, int32_t *idv, TileLds &tl, Val val)
+{
+    static_assert(kRsTile / 64 == 64, "one wavefront scans the words");
+    const int64_t tile = t * kRsTile;
+    const int32_t ef = tfirst[t], el = t + 1 < ntiles ? tfirst[t + 1] : E - 1;
+    if (threadIdx.x < 64) tl.bits[threadIdx.x] = 0;
+    __syncthreads();
+    for (int32_t e = ef + 1 + (int32_t)threadIdx.x; e <= el; e += kBlock) {
+        const int64_t o = (int64_t)off[e] - tile;
+        if (o < 0 || o >= kRsTile) continue;
+        if (EMPTY && off[e + 1] == off[e]) continue;
+        atomicOr(&tl.bits[o >> 6], 1ull << (o & 63));
+        idv[o] = val(e);
+    }
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        const int lane = threadIdx.x;
+        const unsigned long long b = tl.bits[lane];
+        int32_t p = b ? lane * 64 + 63 - __clzll((long long)b) : -1;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            int32_t q = __shfl_up(p, o, 64);
+            if (lane >= o) p = max(p, q);
+        }
+        p = __shfl_up(p, 1, 64);
+        tl.last[lane] = lane ? p : -1;
+    }
+    __syncthreads();
+    return val(ef);
+}
+
+// The value for pin word * 64 + lane of the tile (first: what tile_map returned).
+__device__ __forceinline__ int32_t tile_val(int word, int lane, const int32_t *idv, const TileLds &tl, int32_t first)
+{
+    const unsigned long long m = tl.bits[word] & ((2ull << lane) - 1ull);
+    const int32_t p = m ? word * 64 + 63 - __clzll((long long)m) : tl.last[word];
+    return p >= 0 ? idv[p] : first;
+}
+
+// tfirst of the tiles whose first pin lies in [b, b + d), hyperedge e's pins
+__device__ __forceinline__ void tile_starts(int32_t e, int32_t b, int32_t d, int32_t *tfirst)
+{
+    for (int64_t t = ((int64_t)b + kRsTile - 1) / kRsTile; t * kRsTile < (int64_t)b + d; t++) tfirst[t] = e;
+}
+
+__global__ __launch_bounds__(kBlock) void k_tile_starts(int32_t E, const int32_t *off, int32_t *tfirst)
+{
+    int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e < E) tile_starts((int32_t)e, off[e], off[e + 1] - off[e], tfirst);
+}
+
 // Stable scatter of one tile.  Each wavefront ranks its own 1024 consecutive
 // items (64 a step, in order) against a digit counter row of its own, so no
 // workgroup barrier separates the steps; one scan over the digits then gives
 // every item its place in the tile's digit order, the tile is staged in that
 // order in LDS, and it is written out from there: consecutive threads write
 // consecutive addresses of a digit's run.
+// FIRST: the values are the pins' hyperedges, found from off and tfirst (vin is
+// not read), so the expanded ids are neither written nor read.
 static_assert(kBlock == 256, "one digit per thread");
-__global__ __launch_bounds__(kBlock) void k_rs_scatter(const uint32_t *kin, const int32_t *vin,
+template <bool FIRST>
+__global__ __launch_bounds__(kBlock) void k_rs_scatter(int32_t E, const int32_t *off, const int32_t *tfirst,
+                                                       const uint32_t *kin, const int32_t *vin,
                                                        int64_t n, int shift,
                                                        const uint32_t *offs, int64_t ntiles,
                                                        uint32_t *kout, int32_t *vout)
@@ -67,7 +138,14 @@ __global__ __launch_bounds__(kBlock) void k_rs_scatter(const uint32_t *kin, cons
     for (int r = 0; r < kRsItems; r++) {
         int64_t i = wb + r * 64 + lane;
         keys[r] = i < n ? kin[i] : 0u;
-        vals[r] = i < n ? vin[i] : 0;
+        if (!FIRST) vals[r] = i < n ? vin[i] : 0;
+    }
+    if (FIRST) {
+        // (lv holds the hyperedges' ids until the staging below)
+        __shared__ TileLds tl;
+        const int32_t ef = tile_map<true>(blockIdx.x, ntiles, E, off, tfirst, lv, tl, [](int32_t e) { return e; });
+#pragma unroll
+        for (int r = 0; r < kRsItems; r++) vals[r] = tile_val(w * kRsItems + r, lane, lv, tl, ef);
     }
     for (int d = lane; d < 256; d += 64) wrun[w][d] = 0;
     // rank of each item among the earlier items of its wavefront with its digit
@@ -124,25 +202,6 @@ __global__ __launch_bounds__(kBlock) void k_rs_scatter(const uint32_t *kin, cons
         kout[pos] = key;
         vout[pos] = lv[j];
     }
-}
-
-// pins -> (node, hyperedge) pairs in pin order: the nodes are the pins
-// themselves, so only each pin's hyperedge is written
-struct ExpandPairsOp {
-    const int32_t *off;
-    int32_t *vals;
-    template <int S> __device__ __forceinline__ void run(int64_t vb, int32_t count, const int32_t *list) const;
-};
-
-template <int S>
-__device__ __forceinline__ void ExpandPairsOp::run(int64_t vb, int32_t count, const int32_t *list) const
-{
-    int lane, stride;
-    int32_t e = sched_hedge_at<S>(vb, count, list, lane, stride);
-    if (e < 0) return;
-    int32_t b = off[e], d = off[e + 1] - b;
-    if (!thread_split<S>(d)) return;
-    for (int i = lane; i < d; i += stride) vals[b + i] = e;
 }
 
 // noff[v] = first position of node v in the sorted keys (lower bound)

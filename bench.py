@@ -36,7 +36,7 @@ PHASE_OF = {
                 "parent", "qbuild", "qbuild_block", "qbuild_huge", "dedup", "copy_pins", "classify",
                 "node_ids", "hedge_ids", "incidence", "radix_hist", "radix_scatter", "level_fixup"],
     "refine": ["project", "side_weights", "gain_nodes", "gain_hedges", "gain_lds", "gain_reduce", "gain_stats", "gain_update",
-               "select", "select_pick", "seg_select", "seg_balance", "seg_initial", "balance", "flip",
+               "select", "select_pick", "seg_select", "win_hist", "win_take", "seg_balance", "seg_initial", "balance", "flip",
                "round", "level_bound"],
 }
 
@@ -151,6 +151,7 @@ def cpu_baseline(name, h, k, eps, budget_s):
 # hardware-counter summaries, which name device functions).
 FAMILY_KERNEL = {"gain_nodes": "k_gain_nodes", "gain_hedges": "k_gain_hedges", "select": "k_select_pass",
                  "seg_select": "k_seg_select", "gain_update": "k_gain_update", "seg_balance": "k_seg_fused",
+                 "win_hist": "k_win_hist", "win_take": "k_win_take",
                  "seg_initial": "k_seg_fused"}
 
 

@@ -244,10 +244,10 @@ typedef struct {
                                       whole balance step in one workgroup, with no launch per
                                       round; 0: never (default 131072) */
     int32_t chunk_select_max_nodes; /* levels too large for the one-workgroup selection whose
-                                      segments all have at most this many nodes (capped at
-                                      262144) select each balance round's nodes in chunks of
-                                      16384 nodes, one workgroup each, merged per segment;
-                                      0: never (default 262144) */
+                                      segments all have at most this many nodes (262144 or
+                                      more: of any size) select and move each balance round's
+                                      nodes in chunks, from counts per gain value; the others
+                                      by radix passes; 0: never (default 262144) */
     int32_t graph_rounds;          /* 1: a level's later rounds (from the seventh) are replayed
                                       from three captured hipGraphs instead of launched one
                                       kernel at a time; 0: launched (default 0) */

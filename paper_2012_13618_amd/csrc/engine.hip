@@ -475,25 +475,38 @@ static bool seg_path(const Ctx &cx, const Level &L, int kind)
     return L.maxseg_nodes <= std::min(cx.sched.seg_select_max_nodes, cap);
 }
 
-// Buffers of the chunked balance selection for levels of at most tab_n
-// chunk table entries (none when tab_n is 0).
-static void alloc_chunk_bufs(Arena &ar, Segs &sg, int64_t tab_n)
+// Whether a level's balance selections are windowed (window.hpp): segments too
+// large for one workgroup, up to the schedule's limit (none at its largest
+// value).
+static bool win_path(const Ctx &cx, const Level &L)
 {
-    sg.chunk_cand = nullptr;
-    sg.chunk_tab_n = tab_n;
-    if (tab_n == 0) return;
-    sg.chunk_cand = ar.get<uint64_t>((int64_t)sg.S * kChunkMax * kChunkKeys);
-    sg.chunk_ccnt = ar.get<int32_t>((int64_t)sg.S * kChunkMax);
-    sg.chunk_tab = ar.get<int32_t>(2 * tab_n + 1);
+    const int32_t lim = cx.sched.chunk_select_max_nodes;
+    return !seg_path(cx, L, 1) && lim > 0 && (lim >= kChunkSelectCap || L.maxseg_nodes <= lim);
 }
 
-// Whether a level's balance selections run in chunks (k_seg_select in chunk
-// mode, then k_bal_merge): segments too large for one workgroup, but of at
-// most kChunkMax chunks.
-static bool chunk_path(const Ctx &cx, const Level &L)
+// Buffers of the windowed selections of n levels (none when no level has one).
+static void alloc_win(Ctx &cx, Segs &sg, const Level *lv, int32_t n)
 {
-    return !seg_path(cx, L, 1) && cx.sched.chunk_select_max_nodes > 0 &&
-           L.maxseg_nodes <= std::min<int64_t>(cx.sched.chunk_select_max_nodes, (int64_t)kChunkMax * kChunkNodes);
+    sg.win = WinState{};
+    int64_t chunks = 0;
+    for (int32_t j = 0; j < n; j++)
+        if (win_path(cx, lv[j]))
+            chunks = std::max(chunks, ceil_div(lv[j].N, win_chunk_nodes(lv[j].maxseg_nodes, lv[j].N)) + lv[j].S);
+    if (chunks == 0) return;
+    Arena &ar = *cx.ar;
+    WinState &w = sg.win;
+    const int64_t S = sg.S;
+    w.top = ar.get<int32_t>(4 * S);
+    w.shift = ar.get<int32_t>(4 * S);
+    w.tot = ar.get<unsigned long long>(3 * S * kWinBins);
+    w.rows = ar.get<unsigned long long>(chunks * kWinBins);
+    w.tab = ar.get<int4>(chunks);
+    w.tab_n = chunks;
+    w.pend = ar.get<int32_t>(3 * S);
+    w.moved = w.pend + S;
+    w.zoom = w.pend + 2 * S;
+    w.before = ar.get<int64_t>(S);
+    Fills().add(w.top + 3 * S, S, kWinStart).add(w.shift + 3 * S, S, 0).run(cx.lc);
 }
 
 // Selection and flip of the chosen nodes (Algorithm 3 rounds, Algorithm 5
@@ -507,11 +520,11 @@ static void select_and_flip(Ctx &cx, Level &L, Segs &sg, const int32_t *gain, co
         if (L.maxseg_nodes <= seg_select_max<0, kSegThreadsSmall>())
             launch(cx.lc, "seg_select", 6.0 * L.N, k_seg_select<0, kSegThreadsSmall>, L.S, kSegThreadsSmall, 0,
                    L.S, sel_view(L, sg, gain), sg.st, id_bits(L), (const int32_t *)L.nw, (unsigned long long *)sg.w,
-                   bf, go, ChunkArgs{});
+                   bf, go);
         else
             launch(cx.lc, "seg_select", 6.0 * L.N, k_seg_select<0, kSegThreads>, L.S, kSegThreads, 0, L.S,
                    sel_view(L, sg, gain), sg.st, id_bits(L), (const int32_t *)L.nw, (unsigned long long *)sg.w,
-                   bf, go, ChunkArgs{});
+                   bf, go);
         return;
     }
     run_select(cx, L, sg, gain, go);
@@ -609,9 +622,10 @@ static bool replay_round(LaunchCtx &lc, Segs &sg, RoundGraphs &rg, int64_t ri, R
 // With estimate (balance rounds), go[3] holds the rounds the segments still
 // need as estimated by the last round: the next chunk is that long, and an
 // estimate of zero ends the loop.  round(ri, gc) issues round ri; gc is its
-// active-segment counter, which every kernel of the round checks.
-template <typename Round>
-static int64_t chunked_rounds(Ctx &cx, Segs &sg, int64_t limit, bool estimate, Round round)
+// active-segment counter, which every kernel of the round checks.  check() is
+// issued after each chunk.
+template <typename Round, typename Check>
+static int64_t chunked_rounds(Ctx &cx, Segs &sg, int64_t limit, bool estimate, Round round, Check check)
 {
     LaunchCtx &lc = cx.lc;
     int64_t issued = 0;
@@ -628,6 +642,7 @@ static int64_t chunked_rounds(Ctx &cx, Segs &sg, int64_t limit, bool estimate, R
             else round((int32_t)issued, sg.go + 4 + issued % 3);
             issued++;
         }
+        check();
         BP_HIP(hipMemcpyAsync(cx.info_h, sg.go, 8 * sizeof(int32_t), hipMemcpyDeviceToHost, lc.stream));
         lc.sync(false);
         int32_t *g = (int32_t *)cx.info_h;
@@ -685,7 +700,7 @@ static int64_t initial_rounds(Ctx &cx, Level &L, Segs &sg, int32_t j, int32_t *g
                sg.st, sg.go);
         run_gains(cx, L, sg, gain, !seg_path(cx, L, 0), gc);
         select_and_flip(cx, L, sg, gain, gc);
-    });
+    }, [] {});
 }
 
 static int64_t refine_level(Ctx &cx, Level &L, Segs &sg, int32_t j, int32_t *gain)
@@ -723,6 +738,7 @@ static int64_t refine_level(Ctx &cx, Level &L, Segs &sg, int32_t j, int32_t *gai
         bits = ar.get<uint32_t>(nbits);
         zf.add(bits, nbits, 0u).add(ml.count, 4, 0);
     }
+    if (win_path(cx, L)) zf.add(sg.win.tot, (int64_t)3 * L.S * kWinBins, 0ull).add(sg.win.pend, (int64_t)3 * L.S, 0);
     zf.run(lc);
     // small segments: the whole balance step in one workgroup each; when every
     // segment is small that is all, else the rounds below run the others
@@ -738,18 +754,19 @@ static int64_t refine_level(Ctx &cx, Level &L, Segs &sg, int32_t j, int32_t *gai
     int32_t cap = sg.cand_stride <= 2048 ? 2 * sg.cand_stride : (sg.cand_stride <= 4096 ? sg.cand_stride : 0);
     BalFinish bf{sg.mode, L.nw, sg.need, sg.room, L.side, (unsigned long long *)sg.w, sg.done, sg.stuck, ml,
                  sg.go, sg.bal_moved, sg.st.rsel};
-    // chunked selections: the level's chunk table (buffers of the whole
+    // windowed selections: the level's chunk table (buffers of the whole
     // bisection, sized for its largest level)
-    bool chunk = chunk_path(cx, L);
-    ChunkArgs ca{};
+    const bool win = win_path(cx, L);
+    WinArgs wa{};
     int64_t nct = 0;
-    if (chunk) {
-        nct = ceil_div(L.N, kChunkNodes) + L.S;
-        if (!sg.chunk_cand || nct > sg.chunk_tab_n)
-            throw Error(BP_ERR_DEVICE, "chunked selection buffers missing");
-        int32_t *tseg = sg.chunk_tab, *tbeg = sg.chunk_tab + sg.chunk_tab_n, *tcnt = sg.chunk_tab + 2 * sg.chunk_tab_n;
-        ca = ChunkArgs{tseg, tbeg, tcnt, L.N, sg.chunk_cand, sg.chunk_ccnt};
-        launch(lc, "balance", 0.0, k_chunk_table, 1, 1024, 0, L.S, (const int32_t *)L.nbase, tseg, tbeg, tcnt);
+    if (win) {
+        const int32_t cn = win_chunk_nodes(L.maxseg_nodes, L.N);
+        WinState &w = sg.win;
+        nct = ceil_div(L.N, cn) + L.S;
+        if (!w.rows || nct > w.tab_n) throw Error(BP_ERR_DEVICE, "windowed selection buffers missing");
+        wa = WinArgs{L.S, L.N, w.tab, gain, L.nw, sg.m, sg.mode, L.side, sg.need, sg.room,
+                     (unsigned long long *)sg.w, w, ml, 0, 0, nullptr};
+        launch(lc, "balance", 0.0, k_win_table, 1, 1024, 0, L.S, cn, (const int32_t *)L.nbase, nct, w);
     }
     int64_t lg = std::max<int64_t>(1, std::min<int64_t>(ceil_div((int64_t)L.P / kLogChunk + L.N, kBlock / 64), 1024));
     int64_t ugrid = std::max<int64_t>(1, std::min<int64_t>(ceil_div(nbits, kUpdWords), 2048));
@@ -760,12 +777,15 @@ static int64_t refine_level(Ctx &cx, Level &L, Segs &sg, int32_t j, int32_t *gai
         fill(lc, ubytes, 1, 0ull);
     }
     RoundBal rb{L.S, (const int32_t *)L.nbase, (const unsigned long long *)sg.w, (const int64_t *)sg.max0,
-                (const int64_t *)sg.max1, sg.done, sg.mode, sg.gmask, sg.m, sg.need, sg.room, sg.ccount};
-    int64_t rounds = chunked_rounds(cx, sg, (int64_t)L.N + L.S + 2, true, [&](int32_t ri, const int32_t *gc) {
+                (const int64_t *)sg.max1, sg.done, sg.mode, sg.gmask, sg.m, sg.need, sg.room, sg.ccount, sg.stuck,
+                sg.bal_moved, win ? sg.win : WinState{}};
+    // (a windowed round may only move its window, a few times for each that moves nodes)
+    const int64_t limit = ((int64_t)L.N + L.S + 2) * (win ? 16 : 1);
+    int64_t rounds = chunked_rounds(cx, sg, limit, true, [&](int32_t ri, const int32_t *gc) {
         bool seg = seg_path(cx, L, 1);
         if (ri == 0 || !incr) {
             launch(lc, "round", 0.0, k_round_balance, gs, kBlock, 0, rb, sg.st, sg.go, ri);
-            run_gains(cx, L, sg, gain, !seg && !chunk, gc, incr);
+            run_gains(cx, L, sg, gain, !seg && !win, gc, incr);
         } else {
             // the round's test and the marking of the last round's moves: one launch
             launch(lc, "round", 0.0, k_round_balance_log, gs + lg, kBlock, 0, gs, rb, sg.st, sg.go, ri,
@@ -776,7 +796,7 @@ static int64_t refine_level(Ctx &cx, Level &L, Segs &sg, int32_t j, int32_t *gai
                    (const int32_t *)L.off, (const int32_t *)L.pins, (const int32_t *)L.hw,
                    (const uint8_t *)L.side, (void *)L.cc, L.cc_pk, gain, (const int32_t *)L.bigslot,
                    (const int32_t *)L.lnbig, (const int32_t *)L.ncount, gc, ml.count, ubytes);
-            if (!seg && !chunk)
+            if (!seg && !win)
                 launch(lc, "gain_stats", 10.0 * L.N, k_gain_stats, reduce_grid(L.N), kBlock, 0, L.N,
                    (const int32_t *)L.nseg, (const uint8_t *)sg.gmask, (const uint8_t *)L.side,
                    (const int32_t *)gain, (const uint8_t *)sg.mode, sg.st.tot, sg.st.gmax, sg.st.gmin,
@@ -786,21 +806,23 @@ static int64_t refine_level(Ctx &cx, Level &L, Segs &sg, int32_t j, int32_t *gai
             if (L.maxseg_nodes <= seg_select_max<1, kSegThreadsSmall>())
                 launch(lc, "seg_select", 6.0 * L.N, k_seg_select<1, kSegThreadsSmall>, L.S, kSegThreadsSmall, 0,
                        L.S, sel_view(L, sg, gain), sg.st, id_bits(L), (const int32_t *)L.nw,
-                       (unsigned long long *)sg.w, bf, gc, ChunkArgs{});
+                       (unsigned long long *)sg.w, bf, gc);
             else if (L.maxseg_nodes <= seg_select_max<1, kSegThreadsBal>())
                 launch(lc, "seg_select", 6.0 * L.N, k_seg_select<1, kSegThreadsBal>, L.S, kSegThreadsBal, 0, L.S,
                        sel_view(L, sg, gain), sg.st, id_bits(L), (const int32_t *)L.nw,
-                       (unsigned long long *)sg.w, bf, gc, ChunkArgs{});
+                       (unsigned long long *)sg.w, bf, gc);
             else
                 launch(lc, "seg_select", 6.0 * L.N, k_seg_select<1, kSegThreads>, L.S, kSegThreads, 0, L.S,
                        sel_view(L, sg, gain), sg.st, id_bits(L), (const int32_t *)L.nw,
-                       (unsigned long long *)sg.w, bf, gc, ChunkArgs{});
+                       (unsigned long long *)sg.w, bf, gc);
             return;
         }
-        if (chunk) {
-            launch(lc, "seg_select", 6.0 * L.N, k_seg_select<1, kChunkThreads, true>, nct, kChunkThreads, 0, L.S,
-                   sel_view(L, sg, gain), sg.st, id_bits(L), (const int32_t *)L.nw, (unsigned long long *)sg.w, bf,
-                   gc, ca);
+        if (win) {
+            wa.cur = ri % 3;
+            wa.nxt = (ri + 1) % 3;
+            wa.go = gc;
+            launch(lc, "win_hist", 9.0 * L.N + 16.0 * kWinBins * nct, k_win_hist, nct, kBlock, 0, wa);
+            launch(lc, "win_take", 9.0 * L.N, k_win_take, nct, kBlock, 0, wa);
             return;
         }
         run_select(cx, L, sg, gain, gc, sg.cand_stride);
@@ -808,6 +830,8 @@ static int64_t refine_level(Ctx &cx, Level &L, Segs &sg, int32_t j, int32_t *gai
                sel_view(L, sg, gain), sg.st, sg.ccount, sg.cand, sg.cand_stride, gc);
         launch(lc, "balance", 0.0, k_bal_finish, L.S, 1024, (size_t)cap * 8, L.S, (const int32_t *)sg.ccount,
                sg.cand, sg.cand_stride, cap, bf);
+    }, [&] {
+        if (win) launch(lc, "round", 0.0, k_win_check, gs, kBlock, 0, rb, sg.go);
     });
     if (ubytes) {
         unsigned long long v = 0;
@@ -899,11 +923,7 @@ void bisect_all(Ctx &cx, Level &L0, Segs &sg, int32_t active0)
     int32_t mmax = (int32_t)ceil_sqrt_i64(maxn);
     sg.cand_stride = next_pow2(std::max(mmax, kBalGather));
     sg.cand = ar.get<uint64_t>((int64_t)sg.S * sg.cand_stride);
-    // chunked balance selections, when some level takes them
-    int64_t tab_n = 0;
-    for (auto &x : lv)
-        if (chunk_path(cx, x)) tab_n = std::max<int64_t>(tab_n, ceil_div(x.N, kChunkNodes) + x.S);
-    alloc_chunk_bufs(ar, sg, tab_n);
+    alloc_win(cx, sg, lv.data(), Lmax + 1);
     int32_t *gain = ar.get<int32_t>(lv[0].N);
     Fills()
         .add(sg.st.hist, (int64_t)2 * sg.S * kBins, 0u)
@@ -2255,7 +2275,7 @@ static Segs step_segs(Ctx &cx, Level &L, int32_t k0, int32_t k1, int64_t max0, i
     int32_t mm = (int32_t)ceil_sqrt_i64(L.N);
     sg.cand_stride = next_pow2(std::max(mm, kBalGather));
     sg.cand = cx.ar->get<uint64_t>(sg.cand_stride);
-    alloc_chunk_bufs(*cx.ar, sg, chunk_path(cx, L) ? ceil_div(L.N, kChunkNodes) + L.S : 0);
+    alloc_win(cx, sg, &L, 1);
     return sg;
 }
 

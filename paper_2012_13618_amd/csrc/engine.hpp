@@ -8,6 +8,7 @@
 #include "uncoarsen.hpp"
 #include "balance.hpp"
 #include "transpose.hpp"
+#include "window.hpp"
 
 namespace bp {
 
@@ -26,6 +27,9 @@ struct Schedule {
     int32_t chunk_select_max_nodes = 1 << 18;
     int32_t graph_rounds = 0;
 };
+
+// chunk_select_max_nodes from here on: no limit
+constexpr int32_t kChunkSelectCap = 1 << 18;
 
 constexpr int kCaptureDevices = 64;
 

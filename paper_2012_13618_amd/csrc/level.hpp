@@ -90,6 +90,20 @@ struct SelState {
     int32_t *tick;    // [S] per-segment tickets of the fused picks
 };
 
+// Windowed balance selection (window.hpp); null where no level uses it.
+struct WinState {
+    int32_t *top = nullptr, *shift = nullptr;  // [2][S] the segments' windows, by round parity
+    unsigned long long *tot = nullptr;         // [2][S][kWinBins] segment histograms, by round parity
+    unsigned long long *rows = nullptr;        // [chunks][kWinBins] the chunks' histograms
+    int4 *tab = nullptr;                       // chunk table, tab_n entries
+    int64_t tab_n = 0;
+    // the last round of each segment: 1 while it is not settled, whether it
+    // moved a node, whether it only moved the window; the heavy side's weight
+    // before it
+    int32_t *pend = nullptr, *moved = nullptr, *zoom = nullptr;
+    int64_t *before = nullptr;
+};
+
 // Per-segment bisection state (device arrays; 2S entries where per side).
 struct Segs {
     int32_t S = 0;
@@ -112,10 +126,7 @@ struct Segs {
     int32_t *ccount;          // balance candidates per segment
     uint64_t *cand;           // [S * cand_stride]
     int32_t cand_stride = 0;
-    uint64_t *chunk_cand = nullptr;  // chunked balance selection: [S][kChunkMax][kChunkKeys], or null
-    int32_t *chunk_ccnt = nullptr;   // [S][kChunkMax]
-    int32_t *chunk_tab = nullptr;    // chunk table: segment, first node ([2][chunk_tab_n]), count
-    int64_t chunk_tab_n = 0;
+    WinState win;             // windowed balance selection (window.hpp)
     int32_t *go;              // [8] round counters: [1] last count, [2] rounds run, [3] estimate,
                               // [4..6] per-round active counts (round i uses slot 4 + i % 3)
     SelState st;              // selection state of the 2S lists

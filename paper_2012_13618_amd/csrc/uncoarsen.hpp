@@ -1002,82 +1002,6 @@ template <int KIND, int TH> constexpr int seg_items() { return KIND == 0 ? 16 : 
 template <int KIND, int TH> constexpr int32_t seg_select_max() { return TH * seg_items<KIND, TH>(); }
 constexpr int kSegKeys = 256;                           // balance candidates: ceil(sqrt n) <= 182
 
-// Balance selection of mid-size segments in chunks: each chunk of up to
-// kChunkNodes nodes of a segment (1024 threads, 16 nodes each) orders its
-// best ceil(sqrt n) nodes, then one workgroup per segment merges the chunks'
-// lists.  The union holds the segment's best ceil(sqrt n), so the merge's
-// first ones are those of the whole segment.
-constexpr int kChunkThreads = 1024;
-constexpr int32_t kChunkNodes = 16384;
-constexpr int kChunkMax = 16;      // chunks per segment: segments up to 262144 nodes
-constexpr int kChunkKeys = 512;    // per chunk: ceil(sqrt 262144) = 512 at most
-struct ChunkArgs {
-    const int32_t *seg, *beg, *count;  // chunk table: segment, first node; count[0] chunks
-    int32_t N;                         // the level's nodes (bounds the chunk's loads)
-    uint64_t *cand;                    // [S][kChunkMax][kChunkKeys]: each chunk's best, ascending
-    int32_t *ccnt;                     // [S][kChunkMax]: how many
-};
-
-// The merge of a balancing segment's chunk lists (1024 threads of one
-// workgroup, the last of the segment's chunks): each node of the chunks'
-// ascending lists is ranked among all of them (its index in its
-// own list plus, by binary search, the smaller keys of every other list); the
-// first min(total, m) in order are the segment's chosen nodes.  Then the
-// balance prefix over them (bal_finish_block: one chosen node a thread, as
-// they fit the workgroup).
-__device__ __forceinline__ void bal_merge_seg(int32_t s, const int32_t *nbase, const int32_t *m, ChunkArgs ca,
-                                              BalFinish bf)
-{
-    static_assert(kChunkKeys <= 1024, "the chosen nodes fit the workgroup");
-    __shared__ uint64_t a[kChunkMax * kChunkKeys];
-    __shared__ uint64_t out[kChunkKeys];
-    __shared__ int32_t cnt[kChunkMax];
-    int32_t n = nbase[s + 1] - nbase[s];
-    int ng = (int)((n + kChunkNodes - 1) / kChunkNodes);  // <= kChunkMax, checked by the caller
-    const int32_t tid = threadIdx.x, nslot = ng * kChunkKeys;
-    // every slot of the segment's lists (past a list's count: unused), with the
-    // counts; the segment's balance state is loaded with them
-    const uint64_t *src = ca.cand + (int64_t)s * kChunkMax * kChunkKeys;
-    for (int32_t f = tid; f < nslot; f += 1024) a[f] = src[f];
-    if (tid < kChunkMax) cnt[tid] = tid < ng ? ca.ccnt[s * kChunkMax + tid] : 0;
-    const int h = (bf.mode[s] & kList1) ? 1 : 0;
-    const int64_t nd = bf.need[s], rm = bf.room[s];
-    int64_t bm0 = 0, bm1 = 0;
-    if (tid == 0) {
-        bm0 = bf.bal_moved[2 * s];
-        bm1 = bf.bal_moved[2 * s + 1];
-    }
-    __syncthreads();
-    int32_t tot = 0;
-    for (int q = 0; q < ng; q++) tot += cnt[q];
-    int32_t take = min(tot, m[s]);
-    // list-major slots (a wavefront's keys are neighbours in one list, so
-    // their searches read the same LDS words), the index range rotated by a
-    // wavefront per pass so that no thread ranks the heads of several lists,
-    // the keys with the most lists to search
-    for (int32_t f = tid; f < nslot; f += 1024) {
-        int q = f / kChunkKeys;
-        int32_t i = ((f % kChunkKeys) + 64 * (f / 1024)) % kChunkKeys;
-        if (i >= cnt[q] || i >= take) continue;
-        uint64_t x = a[q * kChunkKeys + i];
-        int32_t rank = i;
-        for (int o = 0; o < ng && rank < take; o++) {
-            if (o == q) continue;
-            const uint64_t *b = a + o * kChunkKeys;
-            int32_t lo = 0, hi = cnt[o];
-            while (lo < hi) {
-                int32_t mid = (lo + hi) >> 1;
-                if (b[mid] < x) lo = mid + 1;
-                else hi = mid;
-            }
-            rank += lo;
-        }
-        if (rank < take) out[rank] = x;
-    }
-    __syncthreads();
-    bal_finish_block(s, out, take, bf, h, nd, rm, bm0, bm1);
-}
-
 // One workgroup per segment of at most seg_select_max<KIND, TH>() nodes: each list's
 // r-th key by the same 12-bit radix select as the multi-workgroup passes,
 // with the segment's gains in registers and the histogram in LDS, then the
@@ -1087,60 +1011,34 @@ __device__ __forceinline__ void bal_merge_seg(int32_t s, const int32_t *nbase, c
 // gathered meanwhile) and the workgroup takes the balance prefix (Algorithm
 // 5).  The chosen set is the one the multi-workgroup path chooses: the same
 // keys, the same r.
-//
-// CH (kind 1 only): one workgroup per chunk of the chunk table instead, whose
-// ordered best nodes go to ca for the merge by the segment's last chunk; node
-// ids in the selection keys are then local to the chunk, which keeps them
-// short.
-template <int KIND, int TH, bool CH = false>
+template <int KIND, int TH>
 __global__ __launch_bounds__(TH) void k_seg_select(int32_t S, SelView sv, SelState st, int idbits_lv,
                                                            const int32_t *nw,
                                                            unsigned long long *segw, BalFinish bf,
-                                                           const int32_t *go, ChunkArgs ca)
+                                                           const int32_t *go)
 {
-    static_assert(!CH || (KIND == 1 && TH * 16 == kChunkNodes), "chunks: balance, 16 nodes a thread");
-    constexpr int kSegItems = CH ? 16 : seg_items<KIND, TH>();
+    constexpr int kSegItems = seg_items<KIND, TH>();
     constexpr int32_t kCap = TH * kSegItems;
-    constexpr int kKeys = CH ? kChunkKeys : kSegKeys;
+    constexpr int kKeys = kSegKeys;
     __shared__ uint32_t hist[kBins];
     __shared__ int64_t lds64[16];
     __shared__ int32_t sbin, sbefore, sin_;
     __shared__ uint64_t keys[kKeys], sorted[KIND == 1 ? kKeys : 1];
     __shared__ uint8_t sdl[kCap];  // the segment's sides
     __shared__ int32_t nkeys;
-    // the round's flag is loaded together with what the block reads next (all
-    // in bounds: the grid never exceeds the segments or the chunk table, and a
-    // chunk entry past the count is not used)
+    // the round's flag is loaded together with what the block reads next
     const int32_t gv = go ? *go : 1;
-    int32_t s, a0, n;
-    uint8_t md;
-    int64_t bnd = 0, brm = 0, bm0 = 0, bm1 = 0;  // balance (one workgroup): the segment's state, loaded early
-    int32_t nld;  // nodes whose gains and sides are loaded (CH: from the level's end, not the segment's)
-    if (CH) {
-        int32_t ci = blockIdx.x;
-        int32_t cc = ca.count[0];
-        s = ca.seg[ci];
-        a0 = ca.beg[ci];
-        if (gv == 0 || ci >= cc) return;
-        nld = min(ca.N - a0, kChunkNodes);
-        n = min(sv.nbase[s + 1] - a0, kChunkNodes);
-        md = sv.mode[s];
-    } else {
-        s = blockIdx.x;
-        a0 = sv.nbase[s];
-        int32_t a1 = sv.nbase[s + 1];
-        md = sv.mode[s];
-        if (KIND == 1) {
-            bnd = bf.need[s];
-            brm = bf.room[s];
-            bm0 = bf.bal_moved[2 * s];
-            bm1 = bf.bal_moved[2 * s + 1];
-        }
-        if (gv == 0) return;
-        n = a1 - a0;
-        nld = n;
+    const int32_t s = blockIdx.x, a0 = sv.nbase[s], n = sv.nbase[s + 1] - a0;
+    const uint8_t md = sv.mode[s];
+    int64_t bnd = 0, brm = 0, bm0 = 0, bm1 = 0;  // balance: the segment's state, loaded early
+    if (KIND == 1) {
+        bnd = bf.need[s];
+        brm = bf.room[s];
+        bm0 = bf.bal_moved[2 * s];
+        bm1 = bf.bal_moved[2 * s + 1];
     }
-    const int idbits = CH ? bitlen_u32((uint32_t)max(n - 1, 0)) : idbits_lv;
+    if (gv == 0) return;
+    const int idbits = idbits_lv;
     int32_t g[kSegItems];
     uint64_t sbits = 0, ebits = 0;  // bit j: item j's side, item j eligible for its side's list
     // per list: size and gain extremes, from the gains just loaded
@@ -1149,19 +1047,17 @@ __global__ __launch_bounds__(TH) void k_seg_select(int32_t S, SelView sv, SelSta
     // memory page of the bytes it covers) and its gains (indices past the
     // segment read its node 0): loads in flight together
     const uint8_t *sp = sv.side + a0;
-    int32_t off0 = (int32_t)((uintptr_t)sp & 3), nwd = (off0 + n + 3) >> 2, nwl = (off0 + nld + 3) >> 2;
+    int32_t off0 = (int32_t)((uintptr_t)sp & 3), nwd = (off0 + n + 3) >> 2;
     const uint32_t *wp = (const uint32_t *)(sp - off0);
     constexpr int kW = kCap / 4 / TH + 1;
     uint32_t xw[kW];
-    // (CH: issued before the segment's bounds arrive; nodes past the segment
-    // are loaded but never used)
-    if ((CH || md) && nld > 0) {
+    if (md && n > 0) {
 #pragma unroll
-        for (int q = 0; q < kW; q++) xw[q] = wp[min(q * TH + (int32_t)threadIdx.x, nwl - 1)];
+        for (int q = 0; q < kW; q++) xw[q] = wp[min(q * TH + (int32_t)threadIdx.x, nwd - 1)];
 #pragma unroll
         for (int j = 0; j < kSegItems; j++) {
             int32_t i = j * TH + (int32_t)threadIdx.x;
-            g[j] = sv.gain[a0 + (i < nld ? i : 0)];
+            g[j] = sv.gain[a0 + (i < n ? i : 0)];
         }
     }
     if (!md) return;
@@ -1301,7 +1197,7 @@ __global__ __launch_bounds__(TH) void k_seg_select(int32_t S, SelView sv, SelSta
             }
         }
     }
-    if (!CH && threadIdx.x == 0) {
+    if (threadIdx.x == 0) {
         st.rsel[2 * s] = rr[0];
         st.rsel[2 * s + 1] = rr[1];
     }
@@ -1341,85 +1237,38 @@ __global__ __launch_bounds__(TH) void k_seg_select(int32_t S, SelView sv, SelSta
     }
     __syncthreads();
     int32_t cnt = nkeys;
-    if (!CH) {
-        // counting order (as block_rank_sort), each chosen node's weight and
-        // incidence range loaded while its rank is counted (for the finish)
-        __shared__ int32_t pw[CH ? 1 : kKeys], pnb[CH ? 1 : kKeys], pne[CH ? 1 : kKeys];
-        const bool logm = bf.ml.cnode != nullptr;
-        int tpc = 1;
-        while (tpc < 16 && cnt * 2 * tpc <= TH) tpc <<= 1;
-        for (int base = 0; base < cnt * tpc; base += TH) {
-            int t = base + (int)threadIdx.x, i = t / tpc, part = t & (tpc - 1);
-            uint64_t x = keys[i < cnt ? i : 0];
-            int32_t v = (int32_t)(uint32_t)(x & 0xffffffffu), xw = 0, xb = 0, xe = 0;
-            if (i < cnt && part == 0) {
-                xw = nw[v];
-                if (logm) {
-                    xb = bf.ml.noff[v];
-                    xe = bf.ml.noff[v + 1];
-                }
+    // counting order (as block_rank_sort), each chosen node's weight and
+    // incidence range loaded while its rank is counted (for the finish)
+    __shared__ int32_t pw[kKeys], pnb[kKeys], pne[kKeys];
+    const bool logm = bf.ml.cnode != nullptr;
+    int tpc = 1;
+    while (tpc < 16 && cnt * 2 * tpc <= TH) tpc <<= 1;
+    for (int base = 0; base < cnt * tpc; base += TH) {
+        int t = base + (int)threadIdx.x, i = t / tpc, part = t & (tpc - 1);
+        uint64_t x = keys[i < cnt ? i : 0];
+        int32_t v = (int32_t)(uint32_t)(x & 0xffffffffu), xw = 0, xb = 0, xe = 0;
+        if (i < cnt && part == 0) {
+            xw = nw[v];
+            if (logm) {
+                xb = bf.ml.noff[v];
+                xe = bf.ml.noff[v + 1];
             }
-            int r = 0;
-            if (i < cnt) {
+        }
+        int r = 0;
+        if (i < cnt) {
 #pragma unroll 8
-                for (int j = part; j < cnt; j += tpc) r += keys[j] < x;
-            }
-            for (int o = 1; o < tpc; o <<= 1) r += __shfl_xor(r, o, 64);
-            if (i < cnt && part == 0) {
-                sorted[r] = x;
-                pw[r] = xw;
-                pnb[r] = xb;
-                pne[r] = xe;
-            }
+            for (int j = part; j < cnt; j += tpc) r += keys[j] < x;
         }
-        __syncthreads();
-        bal_finish_block(s, sorted, cnt, bf, h, bnd, brm, bm0, bm1, BalPre{pw, pnb, pne});
-        return;
-    }
-    block_rank_sort(keys, sorted, cnt);
-    int32_t gi = (a0 - sv.nbase[s]) / kChunkNodes;
-    uint64_t *dst = ca.cand + ((int64_t)s * kChunkMax + gi) * kChunkKeys;
-    for (int32_t i = threadIdx.x; i < cnt; i += TH) dst[i] = sorted[i];
-    if (threadIdx.x == 0) ca.ccnt[s * kChunkMax + gi] = cnt;
-    // the segment's last chunk to finish (ticket) merges the lists
-    __shared__ int32_t last;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int32_t nch = (sv.nbase[s + 1] - sv.nbase[s] + kChunkNodes - 1) / kChunkNodes;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-        last = atomicAdd(&st.tick[s], 1) == nch - 1;
-        if (last) {
-            st.tick[s] = 0;
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        for (int o = 1; o < tpc; o <<= 1) r += __shfl_xor(r, o, 64);
+        if (i < cnt && part == 0) {
+            sorted[r] = x;
+            pw[r] = xw;
+            pnb[r] = xb;
+            pne[r] = xe;
         }
     }
     __syncthreads();
-    if (last) bal_merge_seg(s, sv.nbase, sv.m, ca, bf);
-}
-
-// The chunk table of a level: segment s gets ceil(n_s / kChunkNodes)
-// consecutive entries (its segment and first node).  One workgroup.
-__global__ __launch_bounds__(1024) void k_chunk_table(int32_t S, const int32_t *nbase, int32_t *seg,
-                                                      int32_t *beg, int32_t *count)
-{
-    __shared__ int32_t lds[16];
-    __shared__ int32_t carry;
-    if (threadIdx.x == 0) carry = 0;
-    __syncthreads();
-    for (int32_t base = 0; base < S; base += blockDim.x) {
-        int32_t s = base + (int32_t)threadIdx.x;
-        int32_t a = s < S ? nbase[s] : 0, n = s < S ? nbase[s + 1] - a : 0;
-        int32_t c = (n + kChunkNodes - 1) / kChunkNodes, tot;
-        int32_t at = block_excl_scan(c, lds, &tot) + carry;
-        for (int32_t i = 0; i < c; i++) {
-            seg[at + i] = s;
-            beg[at + i] = a + i * kChunkNodes;
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) carry += tot;
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) count[0] = carry;
+    bal_finish_block(s, sorted, cnt, bf, h, bnd, brm, bm0, bm1, BalPre{pw, pnb, pne});
 }
 
 // ---- moves ---------------------------------------------------------------------------------
@@ -1579,7 +1428,32 @@ struct RoundBal {
     int32_t *m;
     int64_t *need, *room;
     int32_t *ccount;
+    int32_t *stuck;
+    int64_t *bal_moved;
+    WinState win;  // windowed selection: its rounds are settled by the next test
 };
+
+// A windowed round of segment s after the fact: stuck when it moved nothing
+// (and not merely its window), else its share of the level's moved weight.
+__device__ __forceinline__ void win_settle(int32_t s, const RoundBal &rb)
+{
+    const WinState &w = rb.win;
+    if (!w.pend[s]) return;
+    w.pend[s] = 0;
+    if (w.zoom[s]) {
+        w.zoom[s] = 0;
+        return;
+    }
+    if (!w.moved[s]) {
+        rb.stuck[s] = 1;
+        rb.done[s] = 1;
+        return;
+    }
+    w.moved[s] = 0;
+    const int h = (rb.mode[s] & kList1) ? 1 : 0;
+    rb.bal_moved[2 * s] += w.before[s] - (int64_t)rb.segw[2 * s + h];
+    rb.bal_moved[2 * s + 1] += 1;
+}
 
 __device__ __forceinline__ void round_balance_seg(int32_t s, const RoundBal &rb, SelState st, int32_t *go,
                                                   int32_t ri)
@@ -1597,6 +1471,7 @@ __device__ __forceinline__ void round_balance_seg(int32_t s, const RoundBal &rb,
     if (s >= S) return;
     uint8_t md = 0;
     ccount[s] = 0;
+    if (rb.win.pend) win_settle(s, rb);
     if (!done[s]) {
         int64_t w0 = (int64_t)segw[2 * s], w1 = (int64_t)segw[2 * s + 1];
         int h = -1;
@@ -1610,6 +1485,10 @@ __device__ __forceinline__ void round_balance_seg(int32_t s, const RoundBal &rb,
             room[s] = h ? max0[s] - w0 : max1[s] - w1;
             m[s] = (int32_t)ceil_sqrt_i64(nbase[s + 1] - nbase[s]);
             atomicAdd(cur, 1);
+            if (rb.win.pend) {
+                rb.win.pend[s] = 1;
+                rb.win.before[s] = h ? w1 : w0;
+            }
         }
     }
     mode[s] = md;

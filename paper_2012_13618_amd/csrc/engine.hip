@@ -345,9 +345,9 @@ void run_gains(Ctx &cx, Level &L, Segs &sg, int32_t *gain, bool stats, const int
     cx.pins_refined += L.P;
     if (L.gs.rec) {
         GainLdsArgs a{L.gs, L.S, L.off, L.pins, L.hw, L.nbase, sg.gmask, L.side, need_cc ? (void *)L.cc : nullptr,
-                      L.cc_pk, go};
+                      L.cc_pk, need_cc ? sg.n1 : nullptr, go};
         double sums = 4.0 * L.N + 4.0 * L.maxseg_nodes * (L.gs.bound - L.S);
-        double b = 8.0 * L.E + 4.0 * L.P + 1.0 * L.N + (need_cc ? (L.cc_pk ? 4.0 : 8.0) * L.E : 0.0) + sums;
+        double b = 8.0 * L.E + 4.0 * L.P + 1.0 * L.N + (need_cc ? (L.cc_pk ? 8.0 : 12.0) * L.E : 0.0) + sums;
         if (L.maxseg_nodes <= kGlNodesHalf)
             launch(lc, "gain_lds", b, k_gain_lds<kGlNodesHalf>, L.gs.bound, kGlThreads, 0, a);
         else
@@ -366,7 +366,8 @@ void run_gains(Ctx &cx, Level &L, Segs &sg, int32_t *gain, bool stats, const int
     launch(lc, "gain_hedges", hb, k_gain_hedges, hv, kBlock, 0, L.E, (const int32_t *)L.lmid, L.nmid,
            (const int32_t *)L.lbig, L.nbig, (const int32_t *)L.off, (const int32_t *)L.pins,
            (const int32_t *)L.hw, (const int32_t *)L.hseg, (const uint8_t *)sg.gmask,
-           (const uint8_t *)L.side, (void *)L.cc, L.cc_pk, go, (const int32_t *)L.lnbig, (const int32_t *)L.ncount, gain,
+           (const uint8_t *)L.side, (void *)L.cc, L.cc_pk, need_cc ? sg.n1 : (int32_t *)nullptr, go,
+           (const int32_t *)L.lnbig, (const int32_t *)L.ncount, gain,
            L.big_done);
     int32_t nw = (int32_t)std::min<int64_t>(ceil_div(L.nmid_bound, kBlock / 64), kReduceBlocks);
     int64_t nv = reduce_grid(L.N) + nw + L.nchunk_bound;
@@ -791,10 +792,11 @@ static int64_t refine_level(Ctx &cx, Level &L, Segs &sg, int32_t j, int32_t *gai
             launch(lc, "round", 0.0, k_round_balance_log, gs + lg, kBlock, 0, gs, rb, sg.st, sg.go, ri,
                    (const int32_t *)ml.count, (const int32_t *)ml.cnode, (const int32_t *)ml.cbeg,
                    (const int32_t *)L.noff, (const int32_t *)L.inc, bits, (const void *)L.cc, L.cc_pk,
-                   (const uint8_t *)L.side, gain);
+                   sg.n1, (const uint8_t *)L.side, gain);
             launch(lc, "gain_update", 0.0, k_gain_update, ugrid, kBlock, 0, nbits, bits,
                    (const int32_t *)L.off, (const int32_t *)L.pins, (const int32_t *)L.hw,
-                   (const uint8_t *)L.side, (void *)L.cc, L.cc_pk, gain, (const int32_t *)L.bigslot,
+                   (const uint8_t *)L.side, (void *)L.cc, L.cc_pk, (const int32_t *)sg.n1, gain,
+                   (const int32_t *)L.bigslot,
                    (const int32_t *)L.lnbig, (const int32_t *)L.ncount, gc, ml.count, ubytes);
             if (!seg && !win)
                 launch(lc, "gain_stats", 10.0 * L.N, k_gain_stats, reduce_grid(L.N), kBlock, 0, L.N,
@@ -924,6 +926,7 @@ void bisect_all(Ctx &cx, Level &L0, Segs &sg, int32_t active0)
     sg.cand_stride = next_pow2(std::max(mmax, kBalGather));
     sg.cand = ar.get<uint64_t>((int64_t)sg.S * sg.cand_stride);
     alloc_win(cx, sg, lv.data(), Lmax + 1);
+    sg.n1 = ar.get<int32_t>(lv[0].E);  // (the largest level's; one level's rounds at a time)
     int32_t *gain = ar.get<int32_t>(lv[0].N);
     Fills()
         .add(sg.st.hist, (int64_t)2 * sg.S * kBins, 0u)
@@ -2276,6 +2279,7 @@ static Segs step_segs(Ctx &cx, Level &L, int32_t k0, int32_t k1, int64_t max0, i
     sg.cand_stride = next_pow2(std::max(mm, kBalGather));
     sg.cand = cx.ar->get<uint64_t>(sg.cand_stride);
     alloc_win(cx, sg, &L, 1);
+    sg.n1 = cx.ar->get<int32_t>(L.E);
     return sg;
 }
 

@@ -98,8 +98,9 @@ struct GainLdsArgs {
     int32_t S;
     const int32_t *off, *pins, *hw, *nbase;
     const uint8_t *gmask, *side;
-    void *cc;  // contributions for incremental rounds, or null
+    void *cc;  // contributions and counts of pins on side 1, for incremental rounds, or null
     int pk;
+    int32_t *n1;
     const int32_t *go;
 };
 
@@ -130,7 +131,10 @@ __device__ __forceinline__ void gl_hedge(int32_t e, int32_t b, int32_t d, int32_
     if (STRIDE == 64) n1 = wave_sum(n1);
     if (STRIDE == kGlThreads) n1 = block_sum(n1, lds);
     int2 c = hedge_contrib_value(w, d, n1);
-    if (a.cc && lane == 0) cc_put(a.cc, a.pk, e, c);
+    if (a.cc && lane == 0) {
+        cc_put(a.cc, a.pk, e, c);
+        a.n1[e] = n1;
+    }
     if (c.x == 0 && c.y == 0) return;
 #pragma unroll
     for (int k = 0; k < R; k++) {

@@ -57,7 +57,8 @@ template <int S>
 __device__ __forceinline__ void hedge_contrib_one(int32_t e, int lane, int stride, const int32_t *off,
                                                   const int32_t *pins, const int32_t *hw,
                                                   const int32_t *hseg, const uint8_t *gmask,
-                                                  const uint8_t *side, void *cc, int pk, int32_t *lds)
+                                                  const uint8_t *side, void *cc, int pk, int32_t *n1out,
+                                                  int32_t *lds)
 {
     int32_t b = off[e], d = off[e + 1] - b;
     if (!thread_split<S>(d)) return;  // (eight pins' loads in flight at a time below)
@@ -87,15 +88,17 @@ __device__ __forceinline__ void hedge_contrib_one(int32_t e, int lane, int strid
         c.x = n0 == 1 ? w : (n0 == d ? -w : 0);
         c.y = n1 == 1 ? w : (n1 == d ? -w : 0);
         cc_put(cc, pk, e, c);
+        if (n1out) n1out[e] = n1;
     }
 }
 
+// n1out (nullable): the hyperedges' pins on side 1, for incremental rounds.
 __global__ __launch_bounds__(kBlock) void k_gain_hedges(int32_t E, const int32_t *lmid, int32_t nmid,
                                                         const int32_t *lbig, int32_t nbig,
                                                         const int32_t *off, const int32_t *pins,
                                                         const int32_t *hw, const int32_t *hseg,
                                                         const uint8_t *gmask, const uint8_t *side,
-                                                        void *cc, int pk, const int32_t *go,
+                                                        void *cc, int pk, int32_t *n1out, const int32_t *go,
                                                         const int32_t *lnbig, const int32_t *ncount,
                                                         int32_t *gain, int32_t *big_done)
 {
@@ -111,14 +114,14 @@ __global__ __launch_bounds__(kBlock) void k_gain_hedges(int32_t E, const int32_t
     int64_t vb = blockIdx.x;
     if (vb < ns) {
         int64_t e = xcd_block(vb, ns) * kBlock + threadIdx.x;
-        if (e < E) hedge_contrib_one<SMALL>((int32_t)e, 0, 1, off, pins, hw, hseg, gmask, side, cc, pk, lds);
+        if (e < E) hedge_contrib_one<SMALL>((int32_t)e, 0, 1, off, pins, hw, hseg, gmask, side, cc, pk, n1out, lds);
     } else if (vb < ns + nw) {
         int64_t i = (vb - ns) * (kBlock / 64) + (threadIdx.x >> 6);
         if (i < nmid)
-            hedge_contrib_one<WAVE>(lmid[i], threadIdx.x & 63, 64, off, pins, hw, hseg, gmask, side, cc, pk, lds);
+            hedge_contrib_one<WAVE>(lmid[i], threadIdx.x & 63, 64, off, pins, hw, hseg, gmask, side, cc, pk, n1out, lds);
     } else if (vb - ns - nw < nbig) {
         hedge_contrib_one<BLOCK>(lbig[vb - ns - nw], threadIdx.x, blockDim.x, off, pins, hw, hseg, gmask,
-                                 side, cc, pk, lds);
+                                 side, cc, pk, n1out, lds);
     }
 }
 
@@ -130,6 +133,9 @@ __global__ __launch_bounds__(kBlock) void k_gain_hedges(int32_t E, const int32_t
 // with one atomic (none when they are all set already).  Here: blocks b of nb
 // (kBlock threads each) of the marking of the n logged chunks.
 //
+// Each hyperedge's count of pins on side 1 (n1) follows the move, one atomic an
+// incidence; the gain update reads the counts and not the pins.
+//
 // It also settles the moved node's side change in its gain.  The gain update
 // that follows treats every pin as unmoved (new contribution minus old, both
 // for the pin's side now); a node that moved from side o to side s had gained
@@ -138,8 +144,8 @@ __global__ __launch_bounds__(kBlock) void k_gain_hedges(int32_t E, const int32_t
 // update reads one side byte per pin and no move flags.
 __device__ __forceinline__ void log_hedges_blocks(int64_t b, int64_t nb, int32_t n, const int32_t *cnode,
                                                   const int32_t *cbeg, const int32_t *noff, const int32_t *inc,
-                                                  uint32_t *bits, const void *cc, int pk, const uint8_t *side,
-                                                  int32_t *gain)
+                                                  uint32_t *bits, const void *cc, int pk, int32_t *n1,
+                                                  const uint8_t *side, int32_t *gain)
 {
     int lane = threadIdx.x & 63;
     const int64_t wpb = kBlock / 64;
@@ -151,6 +157,7 @@ __device__ __forceinline__ void log_hedges_blocks(int64_t b, int64_t nb, int32_t
         int sv = side[v];
         int32_t corr = 0;
         if (valid) {
+            atomicAdd(&n1[e], sv ? 1 : -1);
             int2 oc = cc_get(cc, pk, e);
             corr = sv ? oc.y - oc.x : oc.x - oc.y;
         }
@@ -200,57 +207,16 @@ __device__ __forceinline__ void add_gain(int32_t u, int32_t delta, const int32_t
 constexpr int kUpdWords = 64;                // bitmap words a workgroup sweeps per step
 constexpr int kUpdChunk = 8;                 // ... as 8 chunks of this many words
 constexpr int kUpdQueue = kUpdWords * 32;  // hyperedges those words can hold
-constexpr int kUpdWaveMax = 512;           // larger marked hyperedges: the whole workgroup
-constexpr int kUpdHugeRegs = 8;            // ... whose pins fit kUpdHugeRegs a thread in registers
+constexpr int kUpdWaveMax = 2048;          // larger changed hyperedges: the whole workgroup
 
-// recount of hyperedge e (pins b .. b + d, d <= kSmallMax) after a round:
-// its new contribution, with each pin's gain change added
-__device__ __forceinline__ int2 recount_small(int32_t e, int32_t b, int32_t d, const int32_t *pins,
-                                              const int32_t *hw, const uint8_t *side, int2 oc,
-                                              const int32_t *bigslot, int32_t *slot, int32_t *gain)
+// The change dc of a hyperedge's contribution to a pin on side 0 / side 1 added
+// to its pins' gains by one thread, eight pins' loads in flight at a time.
+__device__ __forceinline__ void spread_thread(int32_t b, int32_t d, int2 dc, const int32_t *pins,
+                                              const uint8_t *side, const int32_t *bigslot, int32_t *slot,
+                                              int32_t *gain)
 {
-    // straight-line loads (past the degree: pin 0 again), so that they fly together
-    int32_t u[kSmallMax];
-    uint32_t sn[kSmallMax];
-    int32_t n1 = 0;
-#pragma unroll
-    for (int j = 0; j < kSmallMax; j++) u[j] = pins[b + (j < d ? j : 0)];
-#pragma unroll
-    for (int j = 0; j < kSmallMax; j++) sn[j] = side[u[j]];
-#pragma unroll
-    for (int j = 0; j < kSmallMax; j++)
-        if (j < d) n1 += sn[j];
-    int2 nc = hedge_contrib_value(hw[e], d, n1);
-#pragma unroll
-    for (int j = 0; j < kSmallMax; j++)
-        if (j < d) {
-            int32_t delta = sn[j] ? nc.y - oc.y : nc.x - oc.x;
-            if (delta) add_gain(u[j], delta, bigslot, slot, gain);
-        }
-    return nc;
-}
-
-// The same for 9..kHedgeThreadMax pins by one thread, eight pins' loads in
-// flight at a time; the pins are read again (from cache) for the deltas, unless
-// the contribution did not change, when no pin's gain does.
-__device__ __forceinline__ int2 recount_thread(int32_t e, int32_t b, int32_t d, const int32_t *pins,
-                                               const int32_t *hw, const uint8_t *side, int2 oc,
-                                               const int32_t *bigslot, int32_t *slot, int32_t *gain)
-{
-    int32_t n1 = 0;
     for (int32_t i0 = 0; i0 < d; i0 += 8) {
-        int32_t u[8];
-#pragma unroll
-        for (int j = 0; j < 8; j++) u[j] = pins[b + min(i0 + j, d - 1)];
-#pragma unroll
-        for (int j = 0; j < 8; j++) {
-            int32_t x = side[u[j]];
-            if (i0 + j < d) n1 += x;
-        }
-    }
-    int2 nc = hedge_contrib_value(hw[e], d, n1);
-    if (nc.x == oc.x && nc.y == oc.y) return nc;
-    for (int32_t i0 = 0; i0 < d; i0 += 8) {
+        // straight-line loads (past the degree: the last pin again)
         int32_t u[8];
         uint32_t sn[8];
 #pragma unroll
@@ -258,33 +224,55 @@ __device__ __forceinline__ int2 recount_thread(int32_t e, int32_t b, int32_t d, 
 #pragma unroll
         for (int j = 0; j < 8; j++) sn[j] = side[u[j]];
 #pragma unroll
-        for (int j = 0; j < 8; j++)
-            if (i0 + j < d) {
-                int32_t delta = sn[j] ? nc.y - oc.y : nc.x - oc.x;
-                if (delta) add_gain(u[j], delta, bigslot, slot, gain);
-            }
+        for (int j = 0; j < 8; j++) {
+            int32_t delta = sn[j] ? dc.y : dc.x;
+            if (i0 + j < d && delta) add_gain(u[j], delta, bigslot, slot, gain);
+        }
     }
-    return nc;
 }
 
-// Marked hyperedges, found by sweeping the bitmap: recount the sides, replace
-// the contribution, and add the change to every pin's gain, as if no pin had
-// moved (the marking launch has already settled what the moved nodes are
-// owed for changing sides).  Integer sums, so the result equals a
-// recomputation.  The sweep clears the bitmap.
+// The same by lanes lane, lane + stride, ... of a wavefront or workgroup.
+__device__ __forceinline__ void spread_lanes(int32_t b, int32_t d, int2 dc, int lane, int stride,
+                                             const int32_t *pins, const uint8_t *side, const int32_t *bigslot,
+                                             int32_t *slot, int32_t *gain)
+{
+    for (int32_t i0 = 0; i0 < d; i0 += 8 * stride) {
+        int32_t u[8];
+        uint32_t sn[8];
+#pragma unroll
+        for (int k = 0; k < 8; k++) u[k] = pins[b + min(i0 + lane + k * stride, d - 1)];
+#pragma unroll
+        for (int k = 0; k < 8; k++) sn[k] = side[u[k]];
+#pragma unroll
+        for (int k = 0; k < 8; k++) {
+            int32_t delta = sn[k] ? dc.y : dc.x;
+            if (i0 + lane + k * stride < d && delta) add_gain(u[k], delta, bigslot, slot, gain);
+        }
+    }
+}
+
+// Marked hyperedges, found by sweeping the bitmap: the contribution from the
+// count of pins on side 1 that the marking kept, and where it changed, the
+// change added to every pin's gain, as if no pin had moved (the marking launch
+// has already settled what the moved nodes are owed for changing sides).
+// Integer sums, so the result equals a recomputation.  The sweep clears the
+// bitmap.  A hyperedge whose contribution stays - most of those with several
+// pins on both sides - is done without reading a pin, which is what a recount
+// of every marked hyperedge spent its time on (column-net of 617 K rows,
+// k = 32: 29 us a launch, now 16).
 //
 // The bitmap is dealt out in chunks of 8 words (256 hyperedges, in id order),
 // chunk c to workgroup c mod G: a moved node's hyperedges crowd into a few
 // chunks (ids follow locality), and consecutive chunks go to different
 // workgroups.  Each step a workgroup takes 8 of its chunks; one wavefront
-// lists their marked hyperedges in LDS (popcount scan), then degree <= 32 go
-// one per thread, up to 512 one per wavefront, larger ones to the whole
-// workgroup.  When abytes is set (profiling), adds the algorithmic bytes it
-// moved: 4 per bitmap word, per hyperedge 12 (offsets, weight) plus the
-// contribution in and out, 9 per pin (id, side, gain).
+// lists their marked hyperedges in LDS (popcount scan), then changed ones of
+// degree <= 32 go one per thread, up to 2048 one per wavefront, larger ones to
+// the whole workgroup.  When abytes is set (profiling), adds the algorithmic
+// bytes it moved: 4 per bitmap word, per hyperedge 16 (offsets, weight, count)
+// plus the contribution in and out, 9 per pin of a changed one (id, side, gain).
 __global__ __launch_bounds__(kBlock) void k_gain_update(int64_t nwords, uint32_t *bits, const int32_t *off,
                                                         const int32_t *pins, const int32_t *hw,
-                                                        const uint8_t *side, void *cc, int pk,
+                                                        const uint8_t *side, void *cc, int pk, const int32_t *n1,
                                                         int32_t *gain, const int32_t *bigslot,
                                                         const int32_t *lnbig, const int32_t *ncount,
                                                         const int32_t *go, int32_t *logcount,
@@ -292,8 +280,8 @@ __global__ __launch_bounds__(kBlock) void k_gain_update(int64_t nwords, uint32_t
 {
     __shared__ int32_t slot[kUpdSlots];
     __shared__ int32_t queue[kUpdQueue], bigq[kUpdQueue];  // bigq: wavefront ones from the front, workgroup ones from the back
+    __shared__ int2 bigd[kUpdQueue];                       // their changes
     __shared__ int32_t nq, nbq, nhq, npins;
-    __shared__ int32_t lds[16];
     const int32_t gv = go ? *go : 1, nbig = ncount[1];  // loaded together
     if (gv == 0) return;
     // the move log was read by the previous launch: empty it for this round's moves
@@ -326,92 +314,31 @@ __global__ __launch_bounds__(kBlock) void k_gain_update(int64_t nwords, uint32_t
         __syncthreads();
         int32_t n = nq;
         for (int32_t q = threadIdx.x; q < n; q += blockDim.x) {
-            int32_t e = queue[q];
-            int32_t b = off[e], d = off[e + 1] - b;
+            const int32_t e = queue[q], b = off[e], d = off[e + 1] - b;
+            const int2 oc = cc_get(cc, pk, e), nc = hedge_contrib_value(hw[e], d, n1[e]);
+            const int2 dc = make_int2(nc.x - oc.x, nc.y - oc.y);
+            if (dc.x == 0 && dc.y == 0) continue;
+            cc_put(cc, pk, e, nc);
             if (abytes) atomicAdd(&npins, d);
-            if (d <= kSmallMax)
-                cc_put(cc, pk, e, recount_small(e, b, d, pins, hw, side, cc_get(cc, pk, e), bigslot, slot, gain));
-            else if (d <= kHedgeThreadMax)
-                cc_put(cc, pk, e, recount_thread(e, b, d, pins, hw, side, cc_get(cc, pk, e), bigslot, slot, gain));
-            else if (d <= kUpdWaveMax) bigq[atomicAdd(&nbq, 1)] = e;
-            else bigq[kUpdQueue - 1 - atomicAdd(&nhq, 1)] = e;  // front and back never meet
+            if (d <= kHedgeThreadMax) {
+                spread_thread(b, d, dc, pins, side, bigslot, slot, gain);
+                continue;
+            }
+            // front and back never meet
+            int32_t k = d <= kUpdWaveMax ? atomicAdd(&nbq, 1) : kUpdQueue - 1 - atomicAdd(&nhq, 1);
+            bigq[k] = e;
+            bigd[k] = dc;
         }
         __syncthreads();
-        int32_t nbig = nbq, nhuge = nhq;
-        for (int32_t q = wv; q < nbig; q += blockDim.x >> 6) {
-            int32_t e = bigq[q];
-            int32_t b = off[e], d = off[e + 1] - b;
-            int32_t w = hw[e];
-            int2 oc = cc_get(cc, pk, e);
-            // up to kUpdWaveMax / 64 pins a lane, held in registers: their ids,
-            // then their sides, each group of loads in flight together, and
-            // used by both the count and the deltas
-            constexpr int kR = kUpdWaveMax / 64;
-            int32_t u[kR];
-            uint32_t sn[kR];
-#pragma unroll
-            for (int k = 0; k < kR; k++) u[k] = pins[b + min(lane + 64 * k, d - 1)];
-#pragma unroll
-            for (int k = 0; k < kR; k++) sn[k] = side[u[k]];
-            int32_t n1 = 0;
-#pragma unroll
-            for (int k = 0; k < kR; k++)
-                if (lane + 64 * k < d) n1 += sn[k];
-            n1 = wave_sum(n1);
-            int2 nc = hedge_contrib_value(w, d, n1);
-#pragma unroll
-            for (int k = 0; k < kR; k++) {
-                if (lane + 64 * k >= d) continue;
-                int32_t delta = sn[k] ? nc.y - oc.y : nc.x - oc.x;
-                if (delta) add_gain(u[k], delta, bigslot, slot, gain);
-            }
-            if (lane == 0) cc_put(cc, pk, e, nc);
+        int32_t nmid = nbq, nhuge = nhq;
+        for (int32_t q = wv; q < nmid; q += blockDim.x >> 6) {
+            const int32_t e = bigq[q], b = off[e], d = off[e + 1] - b;
+            spread_lanes(b, d, bigd[q], lane, 64, pins, side, bigslot, slot, gain);
         }
         // the largest ones by the whole workgroup, one after another
         for (int32_t q = 0; q < nhuge; q++) {
-            int32_t e = bigq[kUpdQueue - 1 - q];
-            int32_t b = off[e], d = off[e + 1] - b;
-            int2 oc = cc_get(cc, pk, e);
-            int32_t w = hw[e];
-            if (d <= kUpdHugeRegs * kBlock) {
-                // up to kUpdHugeRegs pins a thread in registers (loaded once, in
-                // flight together) for both the count and the deltas
-                int32_t u[kUpdHugeRegs];
-                uint32_t sn[kUpdHugeRegs];
-#pragma unroll
-                for (int k = 0; k < kUpdHugeRegs; k++) u[k] = pins[b + min((int32_t)threadIdx.x + kBlock * k, d - 1)];
-#pragma unroll
-                for (int k = 0; k < kUpdHugeRegs; k++) sn[k] = side[u[k]];
-                int32_t n1 = 0;
-#pragma unroll
-                for (int k = 0; k < kUpdHugeRegs; k++)
-                    if ((int32_t)threadIdx.x + kBlock * k < d) n1 += sn[k];
-                n1 = block_sum(n1, lds);
-                int2 nc = hedge_contrib_value(w, d, n1);
-#pragma unroll
-                for (int k = 0; k < kUpdHugeRegs; k++) {
-                    if ((int32_t)threadIdx.x + kBlock * k >= d) continue;
-                    int32_t delta = sn[k] ? nc.y - oc.y : nc.x - oc.x;
-                    if (delta) add_gain(u[k], delta, bigslot, slot, gain);
-                }
-                __syncthreads();  // every thread has read the old contribution
-                if (threadIdx.x == 0) cc_put(cc, pk, e, nc);
-                continue;
-            }
-            int32_t n1 = 0;
-#pragma unroll 4
-            for (int j = threadIdx.x; j < d; j += blockDim.x) n1 += side[pins[b + j]];
-            n1 = block_sum(n1, lds);
-            int2 nc = hedge_contrib_value(w, d, n1);
-#pragma unroll 4
-            for (int j = threadIdx.x; j < d; j += blockDim.x) {
-                int32_t u = pins[b + j];
-                int sn = side[u];
-                int32_t delta = sn ? nc.y - oc.y : nc.x - oc.x;
-                if (delta) add_gain(u, delta, bigslot, slot, gain);
-            }
-            __syncthreads();  // every thread has read the old contribution
-            if (threadIdx.x == 0) cc_put(cc, pk, e, nc);
+            const int32_t e = bigq[kUpdQueue - 1 - q], b = off[e], d = off[e + 1] - b;
+            spread_lanes(b, d, bigd[kUpdQueue - 1 - q], threadIdx.x, kBlock, pins, side, bigslot, slot, gain);
         }
         __syncthreads();
         if (threadIdx.x == 0) {
@@ -424,7 +351,7 @@ __global__ __launch_bounds__(kBlock) void k_gain_update(int64_t nwords, uint32_t
     for (int i = threadIdx.x; i < nb; i += blockDim.x)
         if (slot[i]) atomicAdd(&gain[lnbig[i]], slot[i]);
     if (abytes && threadIdx.x == 0 && words_done)
-        atomicAdd(abytes, (unsigned long long)(4 * words_done + (pk ? 20 : 28) * hedges_done + 9 * pins_done));
+        atomicAdd(abytes, (unsigned long long)(4 * words_done + (pk ? 24 : 32) * hedges_done + 9 * pins_done));
 }
 
 // eligibility of a node for its list under the segment's selection mode
@@ -1510,7 +1437,7 @@ __global__ __launch_bounds__(kBlock) void k_round_balance_log(int64_t gs, RoundB
                                                               int32_t ri, const int32_t *count,
                                                               const int32_t *cnode, const int32_t *cbeg,
                                                               const int32_t *noff, const int32_t *inc,
-                                                              uint32_t *bits, const void *cc, int pk,
+                                                              uint32_t *bits, const void *cc, int pk, int32_t *n1,
                                                               const uint8_t *side, int32_t *gain)
 {
     if ((int64_t)blockIdx.x < gs) {
@@ -1521,7 +1448,7 @@ __global__ __launch_bounds__(kBlock) void k_round_balance_log(int64_t gs, RoundB
     const int32_t prev = go[4 + (ri + 2) % 3], n = count[0];
     if (prev == 0) return;  // the previous round moved nothing
     log_hedges_blocks((int64_t)blockIdx.x - gs, (int64_t)gridDim.x - gs, n, cnode, cbeg, noff, inc, bits, cc, pk,
-                      side, gain);
+                      n1, side, gain);
 }
 
 

@@ -723,8 +723,15 @@ static int64_t refine_level(Ctx &cx, Level &L, Segs &sg, int32_t j, int32_t *gai
     // balance step: the first round computes every gain; later rounds update
     // the gains from the hyperedges of the nodes the previous round moved
     // incremental gains pay off once a full recomputation is long against
-    // the three short launches they take
-    bool incr = (int64_t)L.P + L.N >= cx.sched.incremental_min_pins && !fuse_all(cx, L);
+    // the three short launches they take - and, where the gains are computed in
+    // LDS, while a round touches few of the hyperedges: ceil(sqrt n) moved nodes
+    // of n touch about 1 / sqrt(n) of the incidences, each hyperedge with all
+    // its pins.  Never recomputed, then recomputed where pins per hyperedge /
+    // sqrt(nodes per segment) is at least 0.5, 0.3, 0.2, 0.1: column-net 617 K
+    // k=32 61.4, 60.6, 59.7, 60.3, 61.3 ms; Random-10M shape 209.6, 203.7,
+    // 203.2, 204.0, 210.4; batch 110.5, 110.7, 106.5, 108.0, 108.9
+    const bool dense = L.gs.rec && L.E > 0 && (double)L.P / L.E >= 0.3 * std::sqrt((double)L.N / L.S);
+    bool incr = (int64_t)L.P + L.N >= cx.sched.incremental_min_pins && !fuse_all(cx, L) && !dense;
     Arena &ar = *cx.ar;
     MoveLog ml{L.noff, nullptr, nullptr, nullptr};
     uint32_t *bits = nullptr;

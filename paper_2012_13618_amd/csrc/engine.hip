@@ -359,26 +359,37 @@ void run_gains(Ctx &cx, Level &L, Segs &sg, int32_t *gain, bool stats, const int
                sg.st.gmin, go);
         return;
     }
-    int64_t hv = std::max<int64_t>(ceil_div(L.E, kBlock) + ceil_div(L.nmid, kBlock / 64) + L.nbig,
-                                   ceil_div(L.nbig_bound, kBlock));
+    // one bit a node / hyperedge where the gathers would leave the L2s
+    uint32_t *sbits = L.N >= kSideBitsMin ? sg.bits : nullptr, *nzb = L.E >= kNzBitsMin ? sg.bits : nullptr;
+    if (L.N >= kSideBitsMin || L.E >= kNzBitsMin)
+        if (!sg.bits) throw Error(BP_ERR_DEVICE, "gain pass buffers missing");
+    if (sbits)
+        launch(lc, "gain_hedges", 1.125 * L.N, k_side_bits, ceil_div(L.N, kBlock), kBlock, 0, L.N,
+               (const uint8_t *)L.side, (unsigned long long *)sbits, go);
+    const int64_t ntiles = L.P > 0 ? ceil_div(L.P, kRsTile) : 0;
     double cb = L.cc_pk ? 4.0 : 8.0;  // bytes of one contribution pair
     double hb = 8.0 * L.E + 4.0 * L.E + 4.0 * L.P + 1.0 * L.P + cb * L.E;
-    launch(lc, "gain_hedges", hb, k_gain_hedges, hv, kBlock, 0, L.E, (const int32_t *)L.lmid, L.nmid,
-           (const int32_t *)L.lbig, L.nbig, (const int32_t *)L.off, (const int32_t *)L.pins,
-           (const int32_t *)L.hw, (const int32_t *)L.hseg, (const uint8_t *)sg.gmask,
-           (const uint8_t *)L.side, (void *)L.cc, L.cc_pk, need_cc ? sg.n1 : (int32_t *)nullptr, go,
-           (const int32_t *)L.lnbig, (const int32_t *)L.ncount, gain,
-           L.big_done);
-    int32_t nw = (int32_t)std::min<int64_t>(ceil_div(L.nmid_bound, kBlock / 64), kReduceBlocks);
-    int64_t nv = reduce_grid(L.N) + nw + L.nchunk_bound;
+    launch(lc, "gain_hedges", hb, k_gain_hedges, std::max(ntiles, ceil_div(L.nbig_bound, kBlock)), kBlock, 0, L.E,
+           ntiles, (const int32_t *)L.off, (const int32_t *)L.pins, (const int32_t *)L.hw, (const int32_t *)L.hseg,
+           (const int32_t *)L.tfirst, (const uint8_t *)sg.gmask, (const uint8_t *)L.side, (const uint32_t *)sbits,
+           (void *)L.cc, L.cc_pk, need_cc ? sg.n1 : (int32_t *)nullptr, go, (const int32_t *)L.lnbig,
+           (const int32_t *)L.ncount, gain, L.big_done);
+    // (the sides' bits are spent)
+    if (nzb)
+        launch(lc, "gain_nodes", (cb + 0.125) * L.E, k_nz_bits, ceil_div(L.E, kBlock), kBlock, 0, L.E,
+               (const void *)L.cc, L.cc_pk, (unsigned long long *)nzb, go);
+    int32_t nw = (int32_t)std::min<int64_t>(ceil_div(L.nmid_bound, kBlock / 64), kGnBlocks);
+    // with stats, at most kGnBlocks workgroups end in the lists' atomics
+    const int64_t ns = stats ? std::min<int64_t>(ceil_div(L.N, kBlock), kGnBlocks) : ceil_div(L.N, kBlock);
+    int64_t nv = ns + nw + L.nchunk_bound;
     double nb = 8.0 * L.N + 4.0 * L.P + cb * L.P + 1.0 * L.N + 4.0 * L.N;
-    launch(lc, "gain_nodes", nb, k_gain_nodes, nv, kBlock, 0, L.N, (const int32_t *)L.lnmid,
+    launch(lc, "gain_nodes", nb, k_gain_nodes, nv, kBlock, 0, L.N, ns, (const int32_t *)L.lnmid,
            (const int32_t *)L.lnbig, (const int32_t *)L.ncount, (const int32_t *)L.noff,
            (const int32_t *)L.inc, (const int32_t *)L.nseg, (const uint8_t *)sg.gmask,
-           (const uint8_t *)L.side, (const void *)L.cc, L.cc_pk, gain, (const uint8_t *)sg.mode,
-           stats ? sg.st.tot : nullptr, sg.st.gmax, sg.st.gmin, go, (const int32_t *)L.chunk_node,
-           (const int32_t *)L.chunk_beg, (const int32_t *)L.chunk_big, (const int32_t *)L.big_chunks,
-           L.big_done, L.S, nw);
+           (const uint8_t *)L.side, (const void *)L.cc, L.cc_pk, (const uint32_t *)nzb, gain,
+           (const uint8_t *)sg.mode, stats ? sg.st.tot : nullptr, sg.st.gmax, sg.st.gmin, go,
+           (const int32_t *)L.chunk_node, (const int32_t *)L.chunk_beg, (const int32_t *)L.chunk_big,
+           (const int32_t *)L.big_chunks, L.big_done, L.S, nw);
 }
 
 // The slab tables of the levels that compute their gains in LDS (one launch);
@@ -418,6 +429,15 @@ static void build_gain_slabs(Ctx &cx, Level *lv, int32_t n)
     if (on.empty()) return;
     int32_t *part = ar.get<int32_t>(parts);
     for (Level *L : on) L->gs.part = part;
+}
+
+// Scratch of the gain passes over levels no larger than L: the counts of
+// incremental rounds and the bits of large levels.
+static void alloc_gain_scratch(Arena &ar, Segs &sg, const Level &L)
+{
+    sg.n1 = ar.get<int32_t>(L.E);
+    sg.bits = L.N >= kSideBitsMin || L.E >= kNzBitsMin ? (uint32_t *)ar.get<uint64_t>(ceil_div(std::max(L.N, L.E), 64))
+                                                      : nullptr;
 }
 
 static int id_bits(const Level &L)
@@ -933,7 +953,7 @@ void bisect_all(Ctx &cx, Level &L0, Segs &sg, int32_t active0)
     sg.cand_stride = next_pow2(std::max(mmax, kBalGather));
     sg.cand = ar.get<uint64_t>((int64_t)sg.S * sg.cand_stride);
     alloc_win(cx, sg, lv.data(), Lmax + 1);
-    sg.n1 = ar.get<int32_t>(lv[0].E);  // (the largest level's; one level's rounds at a time)
+    alloc_gain_scratch(ar, sg, lv[0]);  // (the largest level's; one level's rounds at a time)
     int32_t *gain = ar.get<int32_t>(lv[0].N);
     Fills()
         .add(sg.st.hist, (int64_t)2 * sg.S * kBins, 0u)
@@ -2258,6 +2278,7 @@ bp_status bp_step_gains(const bp_hypergraph *hg, const uint8_t *d_side, int32_t 
     Ctx &cx = g.cx;
     Level L = step_level(cx, hg);
     Segs sg = alloc_segs(*cx.ar, 1);
+    alloc_gain_scratch(*cx.ar, sg, L);
     fill(cx.lc, sg.gmask, 1, (uint8_t)1);
     L.side = const_cast<uint8_t *>(d_side);
     run_gains(cx, L, sg, d_gain, false, nullptr);
@@ -2286,7 +2307,7 @@ static Segs step_segs(Ctx &cx, Level &L, int32_t k0, int32_t k1, int64_t max0, i
     sg.cand_stride = next_pow2(std::max(mm, kBalGather));
     sg.cand = cx.ar->get<uint64_t>(sg.cand_stride);
     alloc_win(cx, sg, &L, 1);
-    sg.n1 = cx.ar->get<int32_t>(L.E);
+    alloc_gain_scratch(*cx.ar, sg, L);
     return sg;
 }
 

@@ -127,6 +127,7 @@ struct Segs {
     uint64_t *cand;           // [S * cand_stride]
     int32_t cand_stride = 0;
     int32_t *n1 = nullptr;    // [E] hyperedges' pins on side 1, in incremental balance rounds
+    uint32_t *bits = nullptr; // one bit a node or hyperedge for the gain passes of large levels
     WinState win;             // windowed balance selection (window.hpp)
     int32_t *go;              // [8] round counters: [1] last count, [2] rounds run, [3] estimate,
                               // [4..6] per-round active counts (round i uses slot 4 + i % 3)

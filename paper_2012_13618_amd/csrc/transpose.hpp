@@ -53,11 +53,27 @@ struct TileLds {
     int32_t last[kRsTile / 64];  // the last start before each word, or -1
 };
 
+// tl.last from tl.bits (the first wavefront works; a barrier on either side)
+__device__ __forceinline__ void tile_last(TileLds &tl)
+{
+    static_assert(kRsTile / 64 == 64, "one wavefront scans the words");
+    if (threadIdx.x >= 64) return;
+    const int lane = threadIdx.x;
+    const unsigned long long b = tl.bits[lane];
+    int32_t p = b ? lane * 64 + 63 - __clzll((long long)b) : -1;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        int32_t q = __shfl_up(p, o, 64);
+        if (lane >= o) p = max(p, q);
+    }
+    p = __shfl_up(p, 1, 64);
+    tl.last[lane] = lane ? p : -1;
+}
+
 template <bool EMPTY, typename Val>
 __device__ __forceinline__ int32_t tile_map(int64_t t, int64_t ntiles, int32_t E, const int32_t *off,
                                             const int32_t *tfirst, int32_t *idv, TileLds &tl, Val val)
 {
-    static_assert(kRsTile / 64 == 64, "one wavefront scans the words");
     const int64_t tile = t * kRsTile;
     const int32_t ef = tfirst[t], el = t + 1 < ntiles ? tfirst[t + 1] : E - 1;
     if (threadIdx.x < 64) tl.bits[threadIdx.x] = 0;
@@ -70,18 +86,7 @@ __device__ __forceinline__ int32_t tile_map(int64_t t, int64_t ntiles, int32_t E
         idv[o] = val(e);
     }
     __syncthreads();
-    if (threadIdx.x < 64) {
-        const int lane = threadIdx.x;
-        const unsigned long long b = tl.bits[lane];
-        int32_t p = b ? lane * 64 + 63 - __clzll((long long)b) : -1;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            int32_t q = __shfl_up(p, o, 64);
-            if (lane >= o) p = max(p, q);
-        }
-        p = __shfl_up(p, 1, 64);
-        tl.last[lane] = lane ? p : -1;
-    }
+    tile_last(tl);
     __syncthreads();
     return val(ef);
 }

@@ -3,11 +3,11 @@
 // Gains (Algorithm 4) take two launches: a hyperedge pass computing what a pin
 // on each side gains from its hyperedge (+w when alone on its side, -w when
 // the hyperedge is uncut), and a node pass summing that over the node's
-// hyperedges.  Each launch covers all degree buckets: virtual blocks
-// [0, ns) take degree <= 8 (hyperedges) / <= 32 (nodes) one per thread, the
-// next ones one listed item per wavefront, the last ones one per workgroup.
-// The node pass also records, per list (one side of one segment), how many
-// nodes are eligible and their largest and smallest gain.
+// hyperedges.  The hyperedge pass takes a tile of pins a workgroup.  The node
+// pass's first blocks take 256 nodes at a time (those of degree <= kGnThread),
+// the next ones one listed larger node per wavefront, the last ones a chunk of
+// a big node.  The node pass also records, per list (one side of one segment),
+// how many nodes are eligible and their largest and smallest gain.
 //
 // Selection of the first r nodes in (gain desc, id asc) order per list is an
 // exact radix select over the pair (u, lid), u = max gain - gain (so ascending
@@ -53,75 +53,116 @@ __device__ __forceinline__ void cc_put(void *cc, int pk, int32_t e, int2 c)
 
 // ---- gains -------------------------------------------------------------------------
 
-template <int S>
-__device__ __forceinline__ void hedge_contrib_one(int32_t e, int lane, int stride, const int32_t *off,
-                                                  const int32_t *pins, const int32_t *hw,
-                                                  const int32_t *hseg, const uint8_t *gmask,
-                                                  const uint8_t *side, void *cc, int pk, int32_t *n1out,
-                                                  int32_t *lds)
+__device__ __forceinline__ int2 hedge_contrib_value(int32_t w, int32_t d, int32_t n1)
 {
-    int32_t b = off[e], d = off[e + 1] - b;
-    if (!thread_split<S>(d)) return;  // (eight pins' loads in flight at a time below)
-    if (!gmask[hseg[e]]) return;
-    int32_t n1 = 0;
-    if (S == SMALL) {
-        // eight pins at a time, straight-line loads (past the degree: the
-        // last pin again) in flight together
-        for (int32_t i0 = 0; i0 < d; i0 += 8) {
-            int32_t u[8];
-#pragma unroll
-            for (int i = 0; i < 8; i++) u[i] = pins[b + min(i0 + i, d - 1)];
-#pragma unroll
-            for (int i = 0; i < 8; i++) {
-                int32_t x = side[u[i]];
-                if (i0 + i < d) n1 += x;
-            }
-        }
-    } else {
-#pragma unroll 4
-        for (int i = lane; i < d; i += stride) n1 += side[pins[b + i]];
-        n1 = group_sum<S>(n1, lds);
-    }
-    if (lane == 0) {
-        int32_t w = hw[e], n0 = d - n1;
-        int2 c;
-        c.x = n0 == 1 ? w : (n0 == d ? -w : 0);
-        c.y = n1 == 1 ? w : (n1 == d ? -w : 0);
-        cc_put(cc, pk, e, c);
-        if (n1out) n1out[e] = n1;
-    }
+    int32_t n0 = d - n1;
+    int2 c;
+    c.x = n0 == 1 ? w : (n0 == d ? -w : 0);
+    c.y = n1 == 1 ? w : (n1 == d ? -w : 0);
+    return c;
 }
 
-// n1out (nullable): the hyperedges' pins on side 1, for incremental rounds.
-__global__ __launch_bounds__(kBlock) void k_gain_hedges(int32_t E, const int32_t *lmid, int32_t nmid,
-                                                        const int32_t *lbig, int32_t nbig,
-                                                        const int32_t *off, const int32_t *pins,
-                                                        const int32_t *hw, const int32_t *hseg,
-                                                        const uint8_t *gmask, const uint8_t *side,
-                                                        void *cc, int pk, int32_t *n1out, const int32_t *go,
-                                                        const int32_t *lnbig, const int32_t *ncount,
-                                                        int32_t *gain, int32_t *big_done)
+// Bits of positions [b, e) of a bit string, b < e.
+__device__ __forceinline__ int32_t count_bits(const unsigned long long *bits, int32_t b, int32_t e)
 {
+    const int32_t w0 = b >> 6, w1 = (e - 1) >> 6;
+    const unsigned long long m0 = ~0ull << (b & 63), m1 = ~0ull >> (63 - ((e - 1) & 63));
+    if (w0 == w1) return __popcll(bits[w0] & m0 & m1);
+    int32_t n = __popcll(bits[w0] & m0) + __popcll(bits[w1] & m1);
+    for (int32_t w = w0 + 1; w < w1; w++) n += __popcll(bits[w]);
+    return n;
+}
+
+// The sides as one bit a node: 1/8 of the bytes, so that the side gathers of
+// levels of very many nodes stay in an L2 (from kSideBitsMin nodes on; below,
+// the bytes are as fast and this pass is saved.  115 M gathers over 10 M
+// nodes: 1.22 ms from bytes, 0.49 from bits; over 1 M: 0.49 and 0.39).
+constexpr int32_t kSideBitsMin = 2 << 20;
+
+__global__ __launch_bounds__(kBlock) void k_side_bits(int32_t N, const uint8_t *side, unsigned long long *bits,
+                                                      const int32_t *go)
+{
+    if (go && *go == 0) return;
+    const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const unsigned long long m = __ballot(v < N && side[v]);
+    if ((threadIdx.x & 63) == 0 && v < N) bits[v >> 6] = m;
+}
+
+// Hyperedge pass of Algorithm 4, a tile of kRsTile pins a workgroup (the
+// hyperedges that start in it): the pins are loaded in order, 16 a thread, their
+// sides gathered and left as one bit a pin in LDS, and a thread a hyperedge
+// counts the bits of its pins.  Four memory round trips, whatever the degrees;
+// one thread walking each hyperedge took two for every eight pins of the
+// wavefront's largest.  Only the last hyperedge can end past the tile's bits:
+// the whole workgroup counts the rest of it.  n1out (nullable): the counts, for
+// incremental rounds.  Bound by the side gathers (sbits or side): 115 M pins
+// over 10 M nodes 2.3 ms, now 0.57; 5.4 M over 1 M 61 us, now 41.
+__global__ __launch_bounds__(kBlock) void k_gain_hedges(int32_t E, int64_t ntiles, const int32_t *off,
+                                                        const int32_t *pins, const int32_t *hw,
+                                                        const int32_t *hseg, const int32_t *tfirst,
+                                                        const uint8_t *gmask, const uint8_t *side,
+                                                        const uint32_t *sbits, void *cc, int pk, int32_t *n1out,
+                                                        const int32_t *go, const int32_t *lnbig,
+                                                        const int32_t *ncount, int32_t *gain, int32_t *big_done)
+{
+    __shared__ unsigned long long bits[kRsTile / 64];
     __shared__ int32_t lds[16];
     if (go && *go == 0) return;
     // big nodes are summed chunk by chunk in the node pass: start them at 0
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < ncount[1]) {
-        gain[lnbig[t]] = 0;
-        big_done[t] = 0;
+    const int64_t z = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (z < ncount[1]) {
+        gain[lnbig[z]] = 0;
+        big_done[z] = 0;
     }
-    int64_t ns = ceil_div(E, kBlock), nw = ceil_div(nmid, kBlock / 64);
-    int64_t vb = blockIdx.x;
-    if (vb < ns) {
-        int64_t e = xcd_block(vb, ns) * kBlock + threadIdx.x;
-        if (e < E) hedge_contrib_one<SMALL>((int32_t)e, 0, 1, off, pins, hw, hseg, gmask, side, cc, pk, n1out, lds);
-    } else if (vb < ns + nw) {
-        int64_t i = (vb - ns) * (kBlock / 64) + (threadIdx.x >> 6);
-        if (i < nmid)
-            hedge_contrib_one<WAVE>(lmid[i], threadIdx.x & 63, 64, off, pins, hw, hseg, gmask, side, cc, pk, n1out, lds);
-    } else if (vb - ns - nw < nbig) {
-        hedge_contrib_one<BLOCK>(lbig[vb - ns - nw], threadIdx.x, blockDim.x, off, pins, hw, hseg, gmask,
-                                 side, cc, pk, n1out, lds);
+    if ((int64_t)blockIdx.x >= ntiles) return;
+    const int64_t t = xcd_block(blockIdx.x, ntiles);
+    const int32_t ef = tfirst[t], el = t + 1 < ntiles ? tfirst[t + 1] : E;
+    const int32_t es = (int64_t)off[ef] == t * kRsTile ? ef : ef + 1;
+    const int32_t ee = el == E || (int64_t)off[el] == (t + 1) * kRsTile ? el : el + 1;
+    if (es >= ee) return;  // (inside one hyperedge)
+    const int32_t p0 = off[es], np = off[ee] - p0, n = min(np, kRsTile);
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    int32_t u[kRsItems];
+    uint32_t x[kRsItems];
+#pragma unroll
+    for (int r = 0; r < kRsItems; r++) u[r] = pins[p0 + min(w * (kRsItems * 64) + r * 64 + lane, n - 1)];
+    if (sbits) {
+#pragma unroll
+        for (int r = 0; r < kRsItems; r++) x[r] = (sbits[u[r] >> 5] >> (u[r] & 31)) & 1;
+    } else {
+#pragma unroll
+        for (int r = 0; r < kRsItems; r++) x[r] = side[u[r]];
+    }
+#pragma unroll
+    for (int r = 0; r < kRsItems; r++) {
+        const unsigned long long m = __ballot(x[r] != 0 && w * (kRsItems * 64) + r * 64 + lane < n);
+        if (lane == 0) bits[w * kRsItems + r] = m;
+    }
+    __syncthreads();
+    for (int32_t e = es + (int32_t)threadIdx.x; e < ee; e += kBlock) {
+        const int32_t b = off[e] - p0, d = off[e + 1] - p0 - b;
+        if (d == 0 || b + d > kRsTile || !gmask[hseg[e]]) continue;
+        const int32_t n1 = count_bits(bits, b, b + d);
+        cc_put(cc, pk, e, hedge_contrib_value(hw[e], d, n1));
+        if (n1out) n1out[e] = n1;
+    }
+    if (np <= kRsTile) return;
+    // (it holds the next tile's first pin)
+    const int32_t b = off[el] - p0, d = off[el + 1] - p0 - b;
+    if (!gmask[hseg[el]]) return;
+    int32_t n1 = 0;
+    for (int32_t i0 = kRsTile + (int32_t)threadIdx.x; i0 < b + d; i0 += 8 * kBlock) {
+        int32_t q[8];
+#pragma unroll
+        for (int k = 0; k < 8; k++) q[k] = pins[p0 + min(i0 + k * kBlock, b + d - 1)];
+#pragma unroll
+        for (int k = 0; k < 8; k++)
+            if (i0 + k * kBlock < b + d) n1 += side[q[k]];
+    }
+    n1 = block_sum(n1, lds) + count_bits(bits, b, kRsTile);
+    if (threadIdx.x == 0) {
+        cc_put(cc, pk, el, hedge_contrib_value(hw[el], d, n1));
+        if (n1out) n1out[el] = n1;
     }
 }
 
@@ -181,15 +222,6 @@ __device__ __forceinline__ void log_hedges_blocks(int64_t b, int64_t nb, int32_t
             if ((old & run) != run) atomicOr(&bits[w], run);
         }
     }
-}
-
-__device__ __forceinline__ int2 hedge_contrib_value(int32_t w, int32_t d, int32_t n1)
-{
-    int32_t n0 = d - n1;
-    int2 c;
-    c.x = n0 == 1 ? w : (n0 == d ? -w : 0);
-    c.y = n1 == 1 ? w : (n1 == d ? -w : 0);
-    return c;
 }
 
 constexpr int kUpdSlots = 1024;  // big nodes whose gain changes gather in LDS first
@@ -362,59 +394,71 @@ __device__ __forceinline__ bool sel_list(int32_t s, int sd, int32_t g, const uin
     return !((md & kGainNonNeg) && g < 0);
 }
 
-template <int S>
-__device__ __forceinline__ void node_gain_one(int32_t v, int lane, int stride, const int32_t *noff,
-                                              const int32_t *inc, const int32_t *nseg,
-                                              const uint8_t *gmask, const uint8_t *side,
-                                              const void *cc, int pk, int32_t *gain, int32_t *lds,
-                                              const uint8_t *mode, int32_t *tot, int32_t *gmax,
-                                              int32_t *gmin, bool stats)
+// Which contributions are not zero, one bit a hyperedge (E > kNzBitsMin): the
+// node pass then gathers the contributions of those only.
+constexpr int32_t kNzBitsMin = 1 << 20;
+
+__global__ __launch_bounds__(kBlock) void k_nz_bits(int32_t E, const void *cc, int pk, unsigned long long *bits,
+                                                    const int32_t *go)
 {
-    int32_t b = noff[v], d = noff[v + 1] - b;
-    if (S == SMALL && d > kNodeSmallMax) return;
-    int32_t s = nseg[v];
-    if (!gmask[s]) return;
-    int sd = side[v];
+    if (go && *go == 0) return;
+    const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    bool nz = false;
+    if (e < E) {
+        const int2 c = cc_get(cc, pk, (int32_t)e);
+        nz = c.x != 0 || c.y != 0;
+    }
+    const unsigned long long m = __ballot(nz);
+    if ((threadIdx.x & 63) == 0 && e < E) bits[e >> 6] = m;
+}
+
+// A lane's share (lane, lane + stride, ...) of the contributions to a node on
+// side sd over its incidences b .. b + d, eight loads in flight at a time.
+__device__ __forceinline__ int32_t gather_sum(int32_t b, int32_t d, int lane, int stride, const int32_t *inc,
+                                              const void *cc, int pk, const uint32_t *nzb, int sd)
+{
     int32_t g = 0;
-    if (S == SMALL) {
-        // eight incidences at a time, straight-line loads (past the degree: the
-        // last incidence again), in flight together
-        for (int i0 = 0; i0 < d; i0 += 8) {
-            int32_t e8[8];
+    for (int32_t i0 = lane; i0 < d; i0 += 8 * stride) {
+        int32_t e[8];
+        bool in[8];
 #pragma unroll
-            for (int k = 0; k < 8; k++) e8[k] = inc[b + min(i0 + k, d - 1)];
-#pragma unroll
-            for (int k = 0; k < 8; k++) {
-                int2 c = cc_get(cc, pk, e8[k]);
-                if (i0 + k < d) g += sd ? c.y : c.x;
-            }
+        for (int k = 0; k < 8; k++) {
+            in[k] = i0 + k * stride < d;
+            e[k] = inc[b + min(i0 + k * stride, d - 1)];
         }
-    } else {
-#pragma unroll 4
-        for (int i = lane; i < d; i += stride) {
-            int2 c = cc_get(cc, pk, inc[b + i]);
+        if (nzb) {
+#pragma unroll
+            for (int k = 0; k < 8; k++) in[k] = in[k] && ((nzb[e[k] >> 5] >> (e[k] & 31)) & 1);
+        }
+#pragma unroll
+        for (int k = 0; k < 8; k++) {
+            if (!in[k]) continue;
+            const int2 c = cc_get(cc, pk, e[k]);
             g += sd ? c.y : c.x;
         }
     }
-    g = group_sum<S>(g, lds);
-    if (lane == 0) {
-        gain[v] = g;
-        if (stats && sel_list(s, sd, g, mode)) {
-            int32_t c = 2 * s + sd;
-            atomicAdd(&tot[c], 1);
-            atomicMax(&gmax[c], g);
-            atomicMin(&gmin[c], g);
-        }
-    }
+    return g;
 }
+
+constexpr int64_t kGnBlocks = 2048;  // workgroups of the node pass that end in the lists' atomics (11 ns each)
+constexpr int32_t kGnThread = 64;    // node degree: staged and summed by a thread; above: a wavefront
 
 // Node pass.  Besides gain[v], per-list counts and gain extremes for the
 // selection that follows (block-aggregated when a block is in one segment).
-__global__ __launch_bounds__(kBlock) void k_gain_nodes(int32_t N, const int32_t *lnmid,
+//
+// The first ns blocks take runs of nodes, 256 at a time: the incidences of
+// those of degree <= kGnThread are loaded in order, 16 a thread, their
+// contributions gathered and staged in LDS, and a thread a node sums its own.
+// (One thread gathering each node's took two memory round trips for every
+// eight incidences of the wavefront's largest node.)  nzb (nullable): the
+// contributions that are not zero.  Bound by the gathers: 115 M incidences of
+// 10 M hyperedges 1.9 ms, now 0.92; 5.4 M of 1.2 M 76 us, now 68.
+__global__ __launch_bounds__(kBlock) void k_gain_nodes(int32_t N, int64_t ns, const int32_t *lnmid,
                                                        const int32_t *lnbig, const int32_t *ncount,
                                                        const int32_t *noff, const int32_t *inc,
                                                        const int32_t *nseg, const uint8_t *gmask,
                                                        const uint8_t *side, const void *cc, int pk,
+                                                       const uint32_t *nzb,
                                                        int32_t *gain, const uint8_t *mode,
                                                        int32_t *tot, int32_t *gmax, int32_t *gmin,
                                                        const int32_t *go, const int32_t *chunk_node,
@@ -428,38 +472,99 @@ __global__ __launch_bounds__(kBlock) void k_gain_nodes(int32_t N, const int32_t 
     if (go && *go == 0) return;
     bool stats = tot != nullptr;
     int32_t cm = ncount[0], ck = ncount[2];
-    int64_t ns = reduce_grid(N);
     int64_t vb = blockIdx.x;
     if (vb < ns) {
-        // nodes of degree <= 32, one per thread, over a contiguous chunk
-        int64_t lo, hi;
-        reduce_chunk(N, ns, xcd_block(vb, ns), lo, hi);
+        __shared__ int32_t val[kRsTile];  // where a node's incidences start, then the gathered contributions
+        __shared__ TileLds tl;
+        __shared__ int32_t carry;
+        // whole 256-node steps, shared out evenly
+        const int64_t per = ceil_div(ceil_div(N, kBlock), ns) * kBlock, lo = xcd_block(vb, ns) * per,
+                      hi = min(lo + per, (int64_t)N);
         if (lo >= hi) return;
         int32_t c0 = 2 * nseg[lo], nl = 2 * nseg[hi - 1] + 2 - c0;
         bool local = nl <= kAggLists;
-        for (int i = threadIdx.x; i < kAggLists; i += blockDim.x) {
-            at[i] = 0;
-            amax[i] = INT32_MIN;
-            amin[i] = INT32_MAX;
-        }
-        __syncthreads();
-        for (int64_t v = lo + threadIdx.x; v < hi; v += blockDim.x) {
-            int32_t b = noff[v], d = noff[v + 1] - b;
-            int32_t s = nseg[v];
-            if (d > kNodeSmallMax || !gmask[s]) continue;
-            int sd = side[v];
-            int32_t g = 0;
-            // eight incidences at a time, straight-line loads in flight together
-            for (int i0 = 0; i0 < d; i0 += 8) {
-                int32_t e8[8];
+        if (stats)
+            for (int i = threadIdx.x; i < kAggLists; i += blockDim.x) {
+                at[i] = 0;
+                amax[i] = INT32_MIN;
+                amin[i] = INT32_MAX;
+            }
+        const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+        for (int64_t base = lo; base < hi; base += kBlock) {
+            const int64_t v = base + threadIdx.x;
+            int32_t b = 0, d = 0, s = 0;
+            int sd = 0;
+            bool on = v < hi;
+            if (on) {
+                b = noff[v];
+                d = noff[v + 1] - b;
+                s = nseg[v];
+                sd = side[v];
+                on = d <= kGnThread && gmask[s];
+            }
+            if (!on) d = 0;
+            int32_t T, st = block_excl_scan(d, lds, &T), g = 0;
+            for (int32_t t0 = 0; t0 < T; t0 += kRsTile) {
+                // each staged position's incidence: st + (b - st)
+                if (threadIdx.x < 64) tl.bits[threadIdx.x] = 0;
+                if (threadIdx.x == 0) carry = 0;
+                __syncthreads();
+                if (d > 0 && st >= t0 && st < t0 + kRsTile) {
+                    atomicOr(&tl.bits[(st - t0) >> 6], 1ull << ((st - t0) & 63));
+                    val[st - t0] = b - st;
+                } else if (st < t0 && st + d > t0) {
+                    carry = b - st;
+                }
+                __syncthreads();
+                tile_last(tl);
+                __syncthreads();
+                int32_t e[kRsItems];
+                bool in[kRsItems];
 #pragma unroll
-                for (int k = 0; k < 8; k++) e8[k] = inc[b + min(i0 + k, d - 1)];
+                for (int r = 0; r < kRsItems; r++) {
+                    const int32_t q = t0 + (r * (kBlock / 64) + w) * 64 + lane;
+                    in[r] = q < T;
+                    e[r] = in[r] ? q + tile_val(r * (kBlock / 64) + w, lane, val, tl, carry) : 0;
+                }
 #pragma unroll
-                for (int k = 0; k < 8; k++) {
-                    int2 c = cc_get(cc, pk, e8[k]);
-                    if (i0 + k < d) g += sd ? c.y : c.x;
+                for (int r = 0; r < kRsItems; r++) e[r] = in[r] ? inc[e[r]] : 0;
+                if (nzb) {
+#pragma unroll
+                    for (int r = 0; r < kRsItems; r++) in[r] = in[r] && ((nzb[e[r] >> 5] >> (e[r] & 31)) & 1);
+                }
+                __syncthreads();
+                if (pk) {
+                    uint32_t c[kRsItems];
+#pragma unroll
+                    for (int r = 0; r < kRsItems; r++) c[r] = in[r] ? ((const uint32_t *)cc)[e[r]] : 0u;
+#pragma unroll
+                    for (int r = 0; r < kRsItems; r++) val[(r * (kBlock / 64) + w) * 64 + lane] = (int32_t)c[r];
+                    __syncthreads();
+                    const int32_t q1 = min(st + d, t0 + kRsTile) - t0;
+                    for (int32_t q = max(st, t0) - t0; q < q1; q++) {
+                        const uint32_t x = (uint32_t)val[q];
+                        g += sd ? (int32_t)(int16_t)(x >> 16) : (int32_t)(int16_t)(x & 0xffffu);
+                    }
+                    __syncthreads();
+                } else {
+                    // a pair of words each: one side's contributions at a time
+                    int2 c[kRsItems];
+#pragma unroll
+                    for (int r = 0; r < kRsItems; r++) c[r] = in[r] ? ((const int2 *)cc)[e[r]] : make_int2(0, 0);
+#pragma unroll 1
+                    for (int h = 0; h < 2; h++) {
+#pragma unroll
+                        for (int r = 0; r < kRsItems; r++)
+                            val[(r * (kBlock / 64) + w) * 64 + lane] = h ? c[r].y : c[r].x;
+                        __syncthreads();
+                        const int32_t q1 = min(st + d, t0 + kRsTile) - t0;
+                        if (sd == h)
+                            for (int32_t q = max(st, t0) - t0; q < q1; q++) g += val[q];
+                        __syncthreads();
+                    }
                 }
             }
+            if (!on) continue;
             gain[v] = g;
             if (!stats || !sel_list(s, sd, g, mode)) continue;
             int32_t c = 2 * s + sd;
@@ -482,7 +587,7 @@ __global__ __launch_bounds__(kBlock) void k_gain_nodes(int32_t N, const int32_t 
                     atomicMin(&gmin[c0 + i], amin[i]);
                 }
     } else if (vb < ns + nw) {
-        // nodes of degree 33..2048, one per wavefront, nw workgroups striding
+        // nodes of degree kGnThread + 1 .. 2048, one per wavefront, nw workgroups striding
         // over the list; with few segments the lists aggregate in LDS
         bool local = 2 * S <= kAggLists;
         for (int i = threadIdx.x; i < kAggLists; i += blockDim.x) {
@@ -497,13 +602,9 @@ __global__ __launch_bounds__(kBlock) void k_gain_nodes(int32_t N, const int32_t 
             int32_t s = nseg[v];
             if (!gmask[s]) continue;
             int32_t b = noff[v], d = noff[v + 1] - b;
+            if (d <= kGnThread) continue;  // (listed from degree 33 on)
             int sd = side[v];
-            int32_t g = 0;
-#pragma unroll 4
-            for (int j = lane; j < d; j += 64) {
-                int2 c = cc_get(cc, pk, inc[b + j]);
-                g += sd ? c.y : c.x;
-            }
+            int32_t g = gather_sum(b, d, lane, 64, inc, cc, pk, nzb, sd);
             g = wave_sum(g);
             if (lane != 0) continue;
             gain[v] = g;
@@ -536,11 +637,7 @@ __global__ __launch_bounds__(kBlock) void k_gain_nodes(int32_t N, const int32_t 
         if (!gmask[s]) return;
         int sd = side[v];
         int32_t b = chunk_beg[q], e = min(b + kNodeChunk, noff[v + 1]);
-        int32_t g = 0;
-        for (int32_t i = b + threadIdx.x; i < e; i += blockDim.x) {
-            int2 c = cc_get(cc, pk, inc[i]);
-            g += sd ? c.y : c.x;
-        }
+        int32_t g = gather_sum(b, e - b, threadIdx.x, kBlock, inc, cc, pk, nzb, sd);
         g = block_sum(g, lds);
         if (threadIdx.x == 0) {
             atomicAdd(&gain[v], g);

@@ -641,12 +641,13 @@ __global__ __launch_bounds__(kBlock) void k_gain_nodes(int32_t N, int64_t ns, co
         g = block_sum(g, lds);
         if (threadIdx.x == 0) {
             atomicAdd(&gain[v], g);
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            if (!stats) return;
+            atomics_done();
             int32_t bi = chunk_big[q];
             if (atomicAdd(&big_done[bi], 1) == big_chunks[bi] - 1) {
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
                 int32_t gv = __hip_atomic_load(&gain[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (stats && sel_list(s, sd, gv, mode)) {
+                if (sel_list(s, sd, gv, mode)) {
                     int32_t c = 2 * s + sd;
                     atomicAdd(&tot[c], 1);
                     atomicMax(&gmax[c], gv);
@@ -858,11 +859,9 @@ __device__ void seg_tickets_pick(int32_t N, int p, int32_t nlists, int idbits, c
             for (int32_t s = sv.nseg[N - 1] + 1 + (int32_t)threadIdx.x; s < S; s += blockDim.x)
                 empty_segment_done(st, s);
     }
+    atomics_done();  // (the histograms are written by atomics alone)
     __syncthreads();
-    if (threadIdx.x == 0) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-        npick = 0;
-    }
+    if (threadIdx.x == 0) npick = 0;
     __syncthreads();
     int32_t sf = sv.nseg[v0], sl = sv.nseg[v1 - 1];
     for (int32_t base = sf; base <= sl; base += blockDim.x) {
@@ -978,9 +977,9 @@ __global__ __launch_bounds__(kBlock) void k_select_pass(int32_t N, int p, int32_
         return;
     }
     // ticket: the last workgroup sees every histogram
+    atomics_done();  // (written by atomics alone)
     __syncthreads();
     if (threadIdx.x == 0) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         int t = atomicAdd(&st.ctl[1], 1);
         last = t == (int)gridDim.x - 1;
         if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");

@@ -97,6 +97,7 @@ void coarsen_level(Ctx &cx, Level &f, Segs &sg, uint8_t *&sact, uint8_t *&sact_n
     c.hbase = ar.get<int32_t>(S + 1);
     alloc_lists(ar, c, E);
     c.tfirst = ar.get<int32_t>(ptiles);
+    c.tnext = ar.get<int2>(4 * ptiles);
     c.counts0 = b.counts;
 
     int64_t initn = std::max<int64_t>(std::max<int64_t>(N, E), T);
@@ -175,6 +176,7 @@ void coarsen_level(Ctx &cx, Level &f, Segs &sg, uint8_t *&sact, uint8_t *&sact_n
                       *wsum = b.wsum;
         const int32_t *foff = f.off;
         int32_t *coff = c.off, *chw = c.hw, *chseg = c.hseg, *csrc = b.csrc, *hbt = b.hb_tmp, *tfirst = c.tfirst;
+        int2 *tnext = c.tnext;
         scan<uint64_t>(
             lc, ar, "hedge_ids", E,
             [=] __device__(int64_t e) -> uint64_t {
@@ -189,7 +191,7 @@ void coarsen_level(Ctx &cx, Level &f, Segs &sg, uint8_t *&sact, uint8_t *&sact_n
                     chw[id] = wsum[e];
                     chseg[id] = s;
                     csrc[id] = foff[e];
-                    tile_starts(id, (int32_t)ex, (int32_t)(val & 0xffffffffu), tfirst);
+                    tile_starts(id, (int32_t)ex, (int32_t)(val & 0xffffffffu), ptiles, tfirst, tnext);
                 }
             },
             b.totEP);
@@ -264,8 +266,9 @@ void build_incidence(Ctx &cx, Level &L)
     uint32_t *tot = ar.get<uint32_t>(1);
     if (!L.tfirst && P > 0) {
         L.tfirst = ar.get<int32_t>(ntiles);
-        launch(lc, "incidence", 4.0 * E, k_tile_starts, ceil_div(E, kBlock), kBlock, 0, E, (const int32_t *)L.off,
-               L.tfirst);
+        L.tnext = ar.get<int2>(4 * ntiles);
+        launch(lc, "incidence", 4.0 * E, k_tile_starts, ceil_div(E, kBlock), kBlock, 0, E, ntiles,
+               (const int32_t *)L.off, L.tfirst, L.tnext);
     }
     // the first pass reads the keys (the pins) in place and finds the values
     // (their hyperedges) from off; it runs for a single node too
@@ -366,24 +369,27 @@ void run_gains(Ctx &cx, Level &L, Segs &sg, int32_t *gain, bool stats, const int
     if (sbits)
         launch(lc, "gain_hedges", 1.125 * L.N, k_side_bits, ceil_div(L.N, kBlock), kBlock, 0, L.N,
                (const uint8_t *)L.side, (unsigned long long *)sbits, go);
-    const int64_t ntiles = L.P > 0 ? ceil_div(L.P, kRsTile) : 0;
+    const bool small = L.P < kGhSmall;
+    const int64_t ntiles = L.P > 0 ? ceil_div(L.P, small ? kGhTile : kRsTile) : 0;
     double cb = L.cc_pk ? 4.0 : 8.0;  // bytes of one contribution pair
     double hb = 8.0 * L.E + 4.0 * L.E + 4.0 * L.P + 1.0 * L.P + cb * L.E;
-    launch(lc, "gain_hedges", hb, k_gain_hedges, std::max(ntiles, ceil_div(L.nbig_bound, kBlock)), kBlock, 0, L.E,
-           ntiles, (const int32_t *)L.off, (const int32_t *)L.pins, (const int32_t *)L.hw, (const int32_t *)L.hseg,
-           (const int32_t *)L.tfirst, (const uint8_t *)sg.gmask, (const uint8_t *)L.side, (const uint32_t *)sbits,
-           (void *)L.cc, L.cc_pk, need_cc ? sg.n1 : (int32_t *)nullptr, go, (const int32_t *)L.lnbig,
-           (const int32_t *)L.ncount, gain, L.big_done);
+    launch(lc, "gain_hedges", hb, small ? &k_gain_hedges<4> : &k_gain_hedges<16>,
+           std::max(ntiles, ceil_div(L.nbig_bound, kBlock)), kBlock, 0, L.E, L.P, ntiles, (const int32_t *)L.off,
+           (const int32_t *)L.pins, (const int32_t *)L.hw, (const int32_t *)L.hseg, (const int2 *)L.tnext,
+           (const uint8_t *)sg.gmask, (const uint8_t *)L.side, (const uint32_t *)sbits, (void *)L.cc, L.cc_pk,
+           need_cc ? sg.n1 : (int32_t *)nullptr, go, (const int32_t *)L.lnbig, (const int32_t *)L.ncount, gain,
+           L.big_done);
     // (the sides' bits are spent)
     if (nzb)
         launch(lc, "gain_nodes", (cb + 0.125) * L.E, k_nz_bits, ceil_div(L.E, kBlock), kBlock, 0, L.E,
                (const void *)L.cc, L.cc_pk, (unsigned long long *)nzb, go);
     int32_t nw = (int32_t)std::min<int64_t>(ceil_div(L.nmid_bound, kBlock / 64), kGnBlocks);
     // with stats, at most kGnBlocks workgroups end in the lists' atomics
+    const bool staged = (int64_t)L.N >= kGnStagedMin;
     const int64_t ns = stats ? std::min<int64_t>(ceil_div(L.N, kBlock), kGnBlocks) : ceil_div(L.N, kBlock);
     int64_t nv = ns + nw + L.nchunk_bound;
     double nb = 8.0 * L.N + 4.0 * L.P + cb * L.P + 1.0 * L.N + 4.0 * L.N;
-    launch(lc, "gain_nodes", nb, k_gain_nodes, nv, kBlock, 0, L.N, ns, (const int32_t *)L.lnmid,
+    launch(lc, "gain_nodes", nb, k_gain_nodes, nv, kBlock, 0, L.N, ns, staged ? 1 : 0, (const int32_t *)L.lnmid,
            (const int32_t *)L.lnbig, (const int32_t *)L.ncount, (const int32_t *)L.noff,
            (const int32_t *)L.inc, (const int32_t *)L.nseg, (const uint8_t *)sg.gmask,
            (const uint8_t *)L.side, (const void *)L.cc, L.cc_pk, (const uint32_t *)nzb, gain,

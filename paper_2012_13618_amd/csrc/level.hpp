@@ -60,6 +60,7 @@ struct Level {
     int32_t cc_pk = 0;          // contributions packed as two int16 (every w(e) < 2^15)
     GainSlabs gs;
     int32_t *tfirst = nullptr;   // hyperedge holding the first pin of each radix tile, once known
+    int2 *tnext = nullptr;       // first hyperedge that starts in each quarter tile or after it, and its first pin
     uint32_t *counts0 = nullptr; // the radix tiles' histograms of the first digit, once taken
 };
 

@@ -99,16 +99,27 @@ __device__ __forceinline__ int32_t tile_val(int word, int lane, const int32_t *i
     return p >= 0 ? idv[p] : first;
 }
 
-// tfirst of the tiles whose first pin lies in [b, b + d), hyperedge e's pins
-__device__ __forceinline__ void tile_starts(int32_t e, int32_t b, int32_t d, int32_t *tfirst)
+// Of the radix tiles whose first pin lies in hyperedge e's pins [b, b + d): tfirst.
+// Of the quarter tiles whose first pin lies in (b, b + d]: tnext, the first
+// hyperedge that starts there or after it and where it starts (e + 1, as no
+// hyperedge with pins starts in between); quarter tile 0's is (0, 0).
+constexpr int kGhTile = kRsTile / 4;
+__device__ __forceinline__ void tile_starts(int32_t e, int32_t b, int32_t d, int64_t ntiles, int32_t *tfirst,
+                                            int2 *tnext)
 {
-    for (int64_t t = ((int64_t)b + kRsTile - 1) / kRsTile; t * kRsTile < (int64_t)b + d; t++) tfirst[t] = e;
+    if (e == 0) tnext[0] = make_int2(0, 0);
+    for (int64_t q = (int64_t)b / kGhTile; q * kGhTile <= (int64_t)b + d && q < 4 * ntiles; q++) {
+        if (q * kGhTile < b) continue;
+        if (q % 4 == 0 && q * kGhTile < (int64_t)b + d) tfirst[q / 4] = e;
+        if (q * kGhTile > b) tnext[q] = make_int2(e + 1, b + d);
+    }
 }
 
-__global__ __launch_bounds__(kBlock) void k_tile_starts(int32_t E, const int32_t *off, int32_t *tfirst)
+__global__ __launch_bounds__(kBlock) void k_tile_starts(int32_t E, int64_t ntiles, const int32_t *off,
+                                                        int32_t *tfirst, int2 *tnext)
 {
     int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < E) tile_starts((int32_t)e, off[e], off[e + 1] - off[e], tfirst);
+    if (e < E) tile_starts((int32_t)e, off[e], off[e + 1] - off[e], ntiles, tfirst, tnext);
 }
 
 // Stable scatter of one tile.  Each wavefront ranks its own 1024 consecutive

@@ -88,24 +88,30 @@ __global__ __launch_bounds__(kBlock) void k_side_bits(int32_t N, const uint8_t *
     if ((threadIdx.x & 63) == 0 && v < N) bits[v >> 6] = m;
 }
 
-// Hyperedge pass of Algorithm 4, a tile of kRsTile pins a workgroup (the
-// hyperedges that start in it): the pins are loaded in order, 16 a thread, their
+// Hyperedge pass of Algorithm 4, a tile of kBlock * R pins a workgroup (the
+// hyperedges that start in it): the pins are loaded in order, R a thread, their
 // sides gathered and left as one bit a pin in LDS, and a thread a hyperedge
-// counts the bits of its pins.  Four memory round trips, whatever the degrees;
-// one thread walking each hyperedge took two for every eight pins of the
-// wavefront's largest.  Only the last hyperedge can end past the tile's bits:
-// the whole workgroup counts the rest of it.  n1out (nullable): the counts, for
-// incremental rounds.  Bound by the side gathers (sbits or side): 115 M pins
-// over 10 M nodes 2.3 ms, now 0.57; 5.4 M over 1 M 61 us, now 41.
-__global__ __launch_bounds__(kBlock) void k_gain_hedges(int32_t E, int64_t ntiles, const int32_t *off,
+// counts the bits of its pins.  Three memory round trips, whatever the
+// degrees; one thread walking each hyperedge took two for every eight pins of
+// the wavefront's largest.  Only the last hyperedge can end past the tile's
+// bits: the whole workgroup counts the rest of it.  n1out (nullable): the
+// counts, for incremental rounds.  Bound by the side gathers (sbits or side):
+// 115 M pins over 10 M nodes 2.3 ms, now 0.57; 5.4 M over 1 M 61 us, now 38.
+// Levels of few pins take quarter tiles (R = 4), as only a tile's latency
+// counts there (93 K pins: R = 16 7.6 us, R = 4 4.9).
+constexpr int64_t kGhSmall = 1 << 20;
+template <int R>
+__global__ __launch_bounds__(kBlock) void k_gain_hedges(int32_t E, int32_t P, int64_t ntiles, const int32_t *off,
                                                         const int32_t *pins, const int32_t *hw,
-                                                        const int32_t *hseg, const int32_t *tfirst,
+                                                        const int32_t *hseg, const int2 *tnext,
                                                         const uint8_t *gmask, const uint8_t *side,
                                                         const uint32_t *sbits, void *cc, int pk, int32_t *n1out,
                                                         const int32_t *go, const int32_t *lnbig,
                                                         const int32_t *ncount, int32_t *gain, int32_t *big_done)
 {
-    __shared__ unsigned long long bits[kRsTile / 64];
+    constexpr int32_t kTile = kBlock * R;
+    static_assert(kTile % kGhTile == 0, "whole quarter tiles");
+    __shared__ unsigned long long bits[kTile / 64];
     __shared__ int32_t lds[16];
     if (go && *go == 0) return;
     // big nodes are summed chunk by chunk in the node pass: start them at 0
@@ -116,42 +122,58 @@ __global__ __launch_bounds__(kBlock) void k_gain_hedges(int32_t E, int64_t ntile
     }
     if ((int64_t)blockIdx.x >= ntiles) return;
     const int64_t t = xcd_block(blockIdx.x, ntiles);
-    const int32_t ef = tfirst[t], el = t + 1 < ntiles ? tfirst[t + 1] : E;
-    const int32_t es = (int64_t)off[ef] == t * kRsTile ? ef : ef + 1;
-    const int32_t ee = el == E || (int64_t)off[el] == (t + 1) * kRsTile ? el : el + 1;
-    if (es >= ee) return;  // (inside one hyperedge)
-    const int32_t p0 = off[es], np = off[ee] - p0, n = min(np, kRsTile);
+    const int2 first = tnext[t * (kTile / kGhTile)];
+    const int2 past = t + 1 < ntiles ? tnext[(t + 1) * (kTile / kGhTile)] : make_int2(E, P);
+    const int32_t es = first.x, ee = past.x;
+    const int32_t p0 = first.y, np = past.y - p0, n = min(np, kTile);
+    if (np <= 0) return;  // (inside one hyperedge, or only empty ones start here)
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    int32_t u[kRsItems];
-    uint32_t x[kRsItems];
+    int32_t u[R];
+    uint32_t x[R];
 #pragma unroll
-    for (int r = 0; r < kRsItems; r++) u[r] = pins[p0 + min(w * (kRsItems * 64) + r * 64 + lane, n - 1)];
+    for (int r = 0; r < R; r++) u[r] = pins[p0 + min(w * (R * 64) + r * 64 + lane, n - 1)];
+    // the thread's first hyperedge, in flight with the pins
+    int32_t hb = 0, he = 0, hs = 0, ww = 0;
+    if (es + (int32_t)threadIdx.x < ee) {
+        hb = off[es + threadIdx.x];
+        he = off[es + threadIdx.x + 1];
+        hs = hseg[es + threadIdx.x];
+        ww = hw[es + threadIdx.x];
+    }
     if (sbits) {
 #pragma unroll
-        for (int r = 0; r < kRsItems; r++) x[r] = (sbits[u[r] >> 5] >> (u[r] & 31)) & 1;
+        for (int r = 0; r < R; r++) x[r] = (sbits[u[r] >> 5] >> (u[r] & 31)) & 1;
     } else {
 #pragma unroll
-        for (int r = 0; r < kRsItems; r++) x[r] = side[u[r]];
+        for (int r = 0; r < R; r++) x[r] = side[u[r]];
     }
 #pragma unroll
-    for (int r = 0; r < kRsItems; r++) {
-        const unsigned long long m = __ballot(x[r] != 0 && w * (kRsItems * 64) + r * 64 + lane < n);
-        if (lane == 0) bits[w * kRsItems + r] = m;
+    for (int r = 0; r < R; r++) {
+        const unsigned long long m = __ballot(x[r] != 0 && w * (R * 64) + r * 64 + lane < n);
+        if (lane == 0) bits[w * R + r] = m;
     }
+    bool on = gmask[hs];
     __syncthreads();
     for (int32_t e = es + (int32_t)threadIdx.x; e < ee; e += kBlock) {
-        const int32_t b = off[e] - p0, d = off[e + 1] - p0 - b;
-        if (d == 0 || b + d > kRsTile || !gmask[hseg[e]]) continue;
-        const int32_t n1 = count_bits(bits, b, b + d);
-        cc_put(cc, pk, e, hedge_contrib_value(hw[e], d, n1));
-        if (n1out) n1out[e] = n1;
+        const int32_t b = hb - p0, d = he - hb;
+        if (d > 0 && b + d <= kTile && on) {
+            const int32_t n1 = count_bits(bits, b, b + d);
+            cc_put(cc, pk, e, hedge_contrib_value(ww, d, n1));
+            if (n1out) n1out[e] = n1;
+        }
+        if (e + kBlock < ee) {
+            hb = off[e + kBlock];
+            he = off[e + kBlock + 1];
+            on = gmask[hseg[e + kBlock]];
+            ww = hw[e + kBlock];
+        }
     }
-    if (np <= kRsTile) return;
-    // (it holds the next tile's first pin)
-    const int32_t b = off[el] - p0, d = off[el + 1] - p0 - b;
+    if (np <= kTile) return;
+    // the one that holds the next tile's first pin
+    const int32_t el = ee - 1, b = off[el] - p0, d = past.y - p0 - b;
     if (!gmask[hseg[el]]) return;
     int32_t n1 = 0;
-    for (int32_t i0 = kRsTile + (int32_t)threadIdx.x; i0 < b + d; i0 += 8 * kBlock) {
+    for (int32_t i0 = kTile + (int32_t)threadIdx.x; i0 < b + d; i0 += 8 * kBlock) {
         int32_t q[8];
 #pragma unroll
         for (int k = 0; k < 8; k++) q[k] = pins[p0 + min(i0 + k * kBlock, b + d - 1)];
@@ -159,7 +181,7 @@ __global__ __launch_bounds__(kBlock) void k_gain_hedges(int32_t E, int64_t ntile
         for (int k = 0; k < 8; k++)
             if (i0 + k * kBlock < b + d) n1 += side[q[k]];
     }
-    n1 = block_sum(n1, lds) + count_bits(bits, b, kRsTile);
+    n1 = block_sum(n1, lds) + count_bits(bits, b, kTile);
     if (threadIdx.x == 0) {
         cc_put(cc, pk, el, hedge_contrib_value(hw[el], d, n1));
         if (n1out) n1out[el] = n1;
@@ -440,6 +462,7 @@ __device__ __forceinline__ int32_t gather_sum(int32_t b, int32_t d, int lane, in
     return g;
 }
 
+constexpr int64_t kGnStagedMin = 1 << 18;
 constexpr int64_t kGnBlocks = 2048;  // workgroups of the node pass that end in the lists' atomics (11 ns each)
 constexpr int32_t kGnThread = 64;    // node degree: staged and summed by a thread; above: a wavefront
 
@@ -449,11 +472,13 @@ constexpr int32_t kGnThread = 64;    // node degree: staged and summed by a thre
 // The first ns blocks take runs of nodes, 256 at a time: the incidences of
 // those of degree <= kGnThread are loaded in order, 16 a thread, their
 // contributions gathered and staged in LDS, and a thread a node sums its own.
-// (One thread gathering each node's took two memory round trips for every
-// eight incidences of the wavefront's largest node.)  nzb (nullable): the
+// On smaller levels (not staged) a thread gathers its node's contributions
+// itself, two memory round trips for every eight incidences of the wavefront's
+// largest node: fewer workgroups than the chip holds, so only their latency
+// counts (12 K nodes 8.4 us, staged 11.2; 1 M nodes 76 us, staged 68).  nzb (nullable): the
 // contributions that are not zero.  Bound by the gathers: 115 M incidences of
 // 10 M hyperedges 1.9 ms, now 0.92; 5.4 M of 1.2 M 76 us, now 68.
-__global__ __launch_bounds__(kBlock) void k_gain_nodes(int32_t N, int64_t ns, const int32_t *lnmid,
+__global__ __launch_bounds__(kBlock) void k_gain_nodes(int32_t N, int64_t ns, int staged, const int32_t *lnmid,
                                                        const int32_t *lnbig, const int32_t *ncount,
                                                        const int32_t *noff, const int32_t *inc,
                                                        const int32_t *nseg, const uint8_t *gmask,
@@ -472,6 +497,7 @@ __global__ __launch_bounds__(kBlock) void k_gain_nodes(int32_t N, int64_t ns, co
     if (go && *go == 0) return;
     bool stats = tot != nullptr;
     int32_t cm = ncount[0], ck = ncount[2];
+    const int32_t thread_max = staged ? kGnThread : kNodeSmallMax;
     int64_t vb = blockIdx.x;
     if (vb < ns) {
         __shared__ int32_t val[kRsTile];  // where a node's incidences start, then the gathered contributions
@@ -500,10 +526,12 @@ __global__ __launch_bounds__(kBlock) void k_gain_nodes(int32_t N, int64_t ns, co
                 d = noff[v + 1] - b;
                 s = nseg[v];
                 sd = side[v];
-                on = d <= kGnThread && gmask[s];
+                on = d <= thread_max && gmask[s];
             }
             if (!on) d = 0;
-            int32_t T, st = block_excl_scan(d, lds, &T), g = 0;
+            int32_t T = 0, st = 0, g = 0;
+            if (staged) st = block_excl_scan(d, lds, &T);
+            else if (d > 0) g = gather_sum(b, d, 0, 1, inc, cc, pk, nzb, sd);
             for (int32_t t0 = 0; t0 < T; t0 += kRsTile) {
                 // each staged position's incidence: st + (b - st)
                 if (threadIdx.x < 64) tl.bits[threadIdx.x] = 0;
@@ -602,7 +630,7 @@ __global__ __launch_bounds__(kBlock) void k_gain_nodes(int32_t N, int64_t ns, co
             int32_t s = nseg[v];
             if (!gmask[s]) continue;
             int32_t b = noff[v], d = noff[v + 1] - b;
-            if (d <= kGnThread) continue;  // (listed from degree 33 on)
+            if (d <= thread_max) continue;  // (listed from degree 33 on)
             int sd = side[v];
             int32_t g = gather_sum(b, d, lane, 64, inc, cc, pk, nzb, sd);
             g = wave_sum(g);

@@ -33,7 +33,7 @@ def graph(n, deg, max_w, seed=1):
 
 @pytest.mark.parametrize("max_w", [1, 70000])
 @pytest.mark.parametrize("deg", [
-    [2], [T], [T - 1, 2], [T - 1, 1, 1], [T, T, 5], [3, 3 * T + 9, 4], [2] * (T // 2) + [3], [1, 0, 0, T + 1, 0, 7, 0],
+    [2], [T], [T - 1, 2], [T - 1, 1, 1], [T, T, 5], [3, 3 * T + 9, 4], [2] * (T // 2) + [3], [1, 0, 0, T + 1, 0, 7, 0], [T, 0, T, 0, 0], [0, 2 * T, 0, 0],
     [64] * 200, [65] * 200, [T // 2 + 1] * 7, list(range(90)),
 ], ids=str)
 def test_tiles(deg, max_w):

@@ -36,7 +36,7 @@ PHASE_OF = {
                 "parent", "qbuild", "qbuild_block", "qbuild_huge", "dedup", "copy_pins", "classify",
                 "node_ids", "hedge_ids", "incidence", "radix_hist", "radix_scatter", "level_fixup"],
     "refine": ["project", "side_weights", "gain_nodes", "gain_hedges", "gain_lds", "gain_reduce", "gain_stats", "gain_update",
-               "select", "select_pick", "seg_select", "win_hist", "win_take", "seg_balance", "seg_initial", "balance", "flip",
+               "select", "select_pick", "seg_select", "seg_levels", "win_hist", "win_take", "seg_balance", "seg_initial", "balance", "flip",
                "round", "level_bound"],
 }
 

@@ -916,6 +916,47 @@ void bisect_all(Ctx &cx, Level &L0, Segs &sg, int32_t active0)
     cx.tree_depth.push_back(l);
     int32_t Lmax = l;
 
+    // the levels at the coarse end whose segments are all small: several a launch
+    int32_t jf = Lmax + 1;
+    while (jf > 0 && fuse_all(cx, lv[jf - 1]) && lv[jf - 1].maxseg_pins <= kFuseLevelPins) jf--;
+    for (int32_t top = Lmax; top >= jf; top -= kFuseLevels) {
+        const int32_t bottom = std::max(jf, top - kFuseLevels + 1);
+        double t0 = trace_on() ? trace_ms() : 0.0;
+        Level &B = lv[bottom];
+        B.side = ar.get<uint8_t>(B.N);
+        FuseLevelsArgs fl{};
+        double bytes = 0.0;
+        for (int32_t j = bottom; j <= top; j++) {
+            const Level &x = lv[j];
+            fl.lv[j - bottom] = FuseLevel{x.off, x.pins, x.hw, x.noff, x.inc, x.nw, x.nbase, x.hbase, x.parent};
+            bytes += 4.0 * x.P + 12.0 * x.N;
+            cx.pins_refined += x.P * (int64_t)std::max(cx.prm.refine_iters, 1);
+        }
+        fl.S = L0.S;
+        fl.top = top;
+        fl.bottom = bottom;
+        fl.iters = cx.prm.refine_iters;
+        fl.side = B.side;
+        fl.side_in = top < Lmax ? lv[top + 1].side : nullptr;
+        fl.nbase_in = top < Lmax ? lv[top + 1].nbase : nullptr;
+        fl.fa.max0 = sg.max0;
+        fl.fa.max1 = sg.max1;
+        fl.fa.segw = (unsigned long long *)sg.w;
+        fl.fa.stuck = sg.stuck;
+        fl.fa.coarsest = sg.coarsest;
+        fl.fa.k0 = sg.k0;
+        fl.fa.k1 = sg.k1;
+        fl.fa.W = sg.W;
+        launch(lc, "seg_levels", bytes, k_seg_levels, L0.S, kFuseThreads, 0, fl);
+        if (trace_on())
+            fprintf(stderr, "[bp] levels %d..%d: S=%d N=%d P=%d in one launch  %.3f ms\n", top, bottom, B.S, B.N, B.P,
+                    trace_ms() - t0);
+    }
+    if (jf == 0) {
+        L0.side = lv[0].side;
+        return;
+    }
+
     // per level: a bound on the gain span, for the number of selection passes
     {
         unsigned long long *bd = ar.get<unsigned long long>(2 * (Lmax + 1));
@@ -968,7 +1009,7 @@ void bisect_all(Ctx &cx, Level &L0, Segs &sg, int32_t active0)
         .add(sg.st.rsel, (int64_t)2 * sg.S, 0)
         .run(lc);
 
-    for (int32_t j = Lmax; j >= 0; j--) {
+    for (int32_t j = jf - 1; j >= 0; j--) {
         Level &L = lv[j];
         L.side = ar.get<uint8_t>(L.N);
         // (and the segments' side weights zeroed)

@@ -240,9 +240,10 @@ typedef struct {
     int32_t fused_pick_lists;      /* up to this many lists the digit picks run in the histogram
                                       launch's last workgroup, above in per-segment ones,
                                       0..4096 (default 8) */
-    int32_t fuse_max_pins;         /* segments of at most 8192 nodes and this many pins run their
-                                      whole balance step in one workgroup, with no launch per
-                                      round; 0: never (default 131072) */
+    int32_t fuse_max_pins;         /* segments of at most 8192 nodes and this many pins (eight times
+                                      as many on levels of 128 segments and more) run their whole
+                                      balance step in one workgroup, with no launch per round; 0:
+                                      never (default 131072) */
     int32_t chunk_select_max_nodes; /* levels too large for the one-workgroup selection whose
                                       segments all have at most this many nodes (262144 or
                                       more: of any size) select and move each balance round's

@@ -689,10 +689,23 @@ static int64_t chunked_rounds(Ctx &cx, Segs &sg, int64_t limit, bool estimate, R
     }
 }
 
+// Pins up to which a segment of the level runs its rounds in one workgroup:
+// the schedule's, or eight times that where the segments are enough to fill half
+// the chip that way (a round of launches then works on all of them as long as a
+// workgroup on one).  Netlist batches at 1, 4 and 8 times: 96 graphs 41.9, 42.3,
+// 43.7 ms; 112 57.5, 54.9, 56.6; 128 69.7, 68.8, 67.1; 200 81.5, 78.1, 75.6; 256
+// 95.2, 90.5, 84.9.
+constexpr int32_t kFuseManySegs = 128;
+static int32_t fuse_pins(const Ctx &cx, const Level &L)
+{
+    int64_t p = (int64_t)cx.sched.fuse_max_pins * (L.S >= kFuseManySegs ? 8 : 1);
+    return (int32_t)std::min<int64_t>(p, INT32_MAX);
+}
+
 // Whether every segment of the level runs its rounds in one workgroup.
 static bool fuse_all(const Ctx &cx, const Level &L)
 {
-    return cx.sched.fuse_max_pins > 0 && L.maxseg_nodes <= kFuseNodes && L.maxseg_pins <= cx.sched.fuse_max_pins &&
+    return cx.sched.fuse_max_pins > 0 && L.maxseg_nodes <= kFuseNodes && L.maxseg_pins <= fuse_pins(cx, L) &&
            L.maxseg_hedges <= kFuseHedges;
 }
 
@@ -714,7 +727,7 @@ static int64_t initial_rounds(Ctx &cx, Level &L, Segs &sg, int32_t j, int32_t *g
         // small segments: all rounds of Algorithm 3 in one workgroup each.  They
         // end with the loop test false, so the rounds below pass them by.
         FuseArgs fa{L.off, L.pins, L.hw, L.noff, L.inc, L.nw, L.nbase, L.hbase, L.side, sg.max0, sg.max1,
-                    (unsigned long long *)sg.w, sg.done, sg.stuck, sg.go + 2, cx.sched.fuse_max_pins,
+                    (unsigned long long *)sg.w, sg.done, sg.stuck, sg.go + 2, fuse_pins(cx, L),
                     sg.coarsest, sg.k0, sg.k1, sg.W, j};
         launch(lc, "seg_initial", 8.0 * L.P, k_seg_fused<true>, L.S, kFuseThreads, 0, L.S, fa);
         if (fuse_all(cx, L)) return fused_rounds_run(cx, sg.go + 2);
@@ -778,7 +791,7 @@ static int64_t refine_level(Ctx &cx, Level &L, Segs &sg, int32_t j, int32_t *gai
     // segment is small that is all, else the rounds below run the others
     if (cx.sched.fuse_max_pins > 0) {
         FuseArgs fa{L.off, L.pins, L.hw, L.noff, L.inc, L.nw, L.nbase, L.hbase, L.side, sg.max0, sg.max1,
-                    (unsigned long long *)sg.w, sg.done, sg.stuck, sg.go + 2, cx.sched.fuse_max_pins,
+                    (unsigned long long *)sg.w, sg.done, sg.stuck, sg.go + 2, fuse_pins(cx, L),
                     nullptr, nullptr, nullptr, nullptr, 0};
         launch(lc, "seg_balance", 8.0 * L.P, k_seg_fused<false>, L.S, kFuseThreads, 0, L.S, fa);
         if (fuse_all(cx, L)) return fused_rounds_run(cx, sg.go + 2);

@@ -188,93 +188,111 @@ __device__ __forceinline__ uint64_t fp_term(int32_t q, uint64_t salt)
     return mix64((uint64_t)(uint32_t)q + salt);
 }
 
-// Parents of a hyperedge of up to N pins (N a power of two) sorted by one thread
-// in registers by a bitonic network (padding INT32_MAX sorts last), then the
-// distinct ones written in order with their fingerprint.
-template <int N>
-__device__ __forceinline__ void qbuild_regs(int64_t e, int32_t b, int32_t d, const int32_t *pins,
-                                            const int32_t *parent, int32_t *qpins, int32_t *qlen, uint64_t *fp)
+// Parents of a hyperedge of up to N pins (N a power of two; at(i) gives pin i's)
+// sorted by one thread in registers by a network (padding INT32_MAX sorts
+// last), then the distinct ones written in order to list; returns how many, and
+// adds their fingerprint terms to sum.
+template <int N, typename At> __device__ __forceinline__ int32_t qbuild_regs(int32_t *list, int32_t d, uint64_t &sum, At at)
 {
     int32_t q[N];
 #pragma unroll
-    for (int i = 0; i < N; i++) q[i] = i < d ? parent[pins[b + i]] : INT32_MAX;
+    for (int i = 0; i < N; i++) q[i] = i < d ? at(i) : INT32_MAX;
+    if (N == 8) {
+        // odd-even transposition
 #pragma unroll
-    for (int k = 2; k <= N; k <<= 1)
+        for (int r = 0; r < N; r++)
 #pragma unroll
-        for (int j = k >> 1; j > 0; j >>= 1)
-#pragma unroll
-            for (int i = 0; i < N; i++) {
-                int p = i ^ j;
-                if (p > i) {
-                    bool up = (i & k) == 0;
-                    int32_t x = q[i], y = q[p];
-                    bool sw = (x > y) == up;
-                    q[i] = sw ? y : x;
-                    q[p] = sw ? x : y;
-                }
+            for (int i = r & 1; i + 1 < N; i += 2) {
+                int32_t x = q[i], y = q[i + 1];
+                q[i] = min(x, y);
+                q[i + 1] = max(x, y);
             }
-    int32_t len = 0;
-    uint64_t sum = 0;
+    } else {
+        // bitonic
 #pragma unroll
-    for (int i = 0; i < N; i++) {
-        bool first = i < d && (i == 0 || q[i] != q[i - 1]);
-        if (first) {
-            qpins[b + len] = q[i];
-            sum += fp_term(q[i], 0);
-            len++;
-        }
+        for (int k = 2; k <= N; k <<= 1)
+#pragma unroll
+            for (int j = k >> 1; j > 0; j >>= 1)
+#pragma unroll
+                for (int i = 0; i < N; i++) {
+                    int p = i ^ j;
+                    if (p > i) {
+                        const bool up = (i & k) == 0;
+                        const int32_t x = q[i], y = q[p];
+                        q[i] = up ? min(x, y) : max(x, y);
+                        q[p] = up ? max(x, y) : min(x, y);
+                    }
+                }
     }
-    qlen[e] = len >= 2 ? len : 0;
-    fp[e] = fp_finish(sum, len);
+    int32_t len = 0;
+#pragma unroll
+    for (int i = 0; i < N; i++)
+        if (i < d && (i == 0 || q[i] != q[i > 0 ? i - 1 : 0])) {
+            list[len++] = q[i];
+            sum += fp_term(q[i], 0);
+        }
+    return len;
 }
 
-// Third loop of Algorithm 2 for hyperedges of degree <= 8: parents sorted in
-// registers by an odd-even transposition network; 9..16 pins by the bitonic
-// network above (a wavefront's shuffles would cost more per hyperedge; a
-// 32-key network would take registers the common small case needs for
-// occupancy).  Block vb of the one-thread-per-hyperedge sweep.
-constexpr int32_t kQbuildThreadMax = 16;
+// Third loop of Algorithm 2 for hyperedges of up to kQbuildThreadMax pins: one
+// thread each up to 16 pins, the larger ones of the workgroup then half a
+// wavefront each (a listed wavefront for each of them took three times as long:
+// 103 M pins over 8.0 M hyperedges 2.7 ms, now 0.92).  Staging 256 hyperedges'
+// parents in LDS, loaded and written in whole lines, was no faster at 13 pins a
+// hyperedge (1.03 ms) and twice as slow at 3.
+constexpr int32_t kQbuildThreadMax = 32;
+static_assert(kQbuildThreadMax == kHedgeThreadMax, "the lists hold the larger ones");
 __device__ __forceinline__ void qbuild_small(int64_t vb, int32_t E, const int32_t *off, const int32_t *pins,
-                                             const int32_t *hseg, const uint8_t *sact, const int32_t *parent,
-                                             int32_t *qpins, int32_t *qlen, uint64_t *fp)
+                                              const int32_t *hseg, const uint8_t *sact, const int32_t *parent,
+                                              int32_t *qpins, int32_t *qlen, uint64_t *fp)
 {
-    int64_t e = vb * blockDim.x + threadIdx.x;
-    if (e >= E) return;
-    int32_t b = off[e], d = off[e + 1] - b;
-    if (d > kQbuildThreadMax) return;
-    if (!sact[hseg[e]]) {
-        qlen[e] = 0;
-        return;
-    }
-    if (d > kSmallMax) {
-        qbuild_regs<kQbuildThreadMax>(e, b, d, pins, parent, qpins, qlen, fp);
-        return;
-    }
-    int32_t q[kSmallMax];
-#pragma unroll
-    for (int i = 0; i < kSmallMax; i++) q[i] = i < d ? parent[pins[b + i]] : INT32_MAX;
-#pragma unroll
-    for (int r = 0; r < kSmallMax; r++) {
-#pragma unroll
-        for (int i = r & 1; i + 1 < kSmallMax; i += 2) {
-            int32_t x = q[i], y = q[i + 1];
-            q[i] = x < y ? x : y;
-            q[i + 1] = x < y ? y : x;
+    __shared__ int32_t queue[kBlock], nq;
+    if (threadIdx.x == 0) nq = 0;
+    __syncthreads();
+    const int64_t e = vb * kBlock + threadIdx.x;
+    if (e < E) {
+        const int32_t b = off[e], d = off[e + 1] - b;
+        if (d <= kQbuildThreadMax) {
+            if (!sact[hseg[e]]) {
+                qlen[e] = 0;
+            } else if (d > 16) {
+                queue[atomicAdd(&nq, 1)] = (int32_t)e;
+            } else {
+                auto at = [=](int i) { return parent[pins[b + i]]; };
+                uint64_t sum = 0;
+                const int32_t len = d <= 8 ? qbuild_regs<8>(qpins + b, d, sum, at) : qbuild_regs<16>(qpins + b, d, sum, at);
+                qlen[e] = len >= 2 ? len : 0;
+                fp[e] = fp_finish(sum, len);
+            }
         }
     }
-    int32_t len = 0;
-    uint64_t sum = 0;
+    __syncthreads();
+    const int lane = threadIdx.x & 63, l = lane & 31;
+    const int32_t n = nq;
+    for (int32_t k = 2 * (threadIdx.x >> 6); k < n; k += kBlock / 32) {
+        const int32_t i = min(k + (lane >> 5), n - 1);  // (the last one twice over, alike)
+        const int32_t h = queue[i], b = off[h], d = off[h + 1] - b;
+        int32_t x = l < d ? parent[pins[b + l]] : INT32_MAX;
 #pragma unroll
-    for (int i = 0; i < kSmallMax; i++) {
-        bool first = i < d && (i == 0 || q[i] != q[i - 1]);
-        if (first) {
-            qpins[b + len] = q[i];
-            sum += fp_term(q[i], 0);
-            len++;
+        for (int kk = 2; kk <= 32; kk <<= 1)
+#pragma unroll
+            for (int j = kk >> 1; j > 0; j >>= 1) {
+                const int32_t y = __shfl_xor(x, j, 64);
+                x = ((l & kk) == 0) == ((l & j) == 0) ? min(x, y) : max(x, y);
+            }
+        const int32_t before = __shfl_up(x, 1, 64);
+        const bool first = l < d && (l == 0 || x != before);
+        const uint32_t m = (uint32_t)(__ballot(first) >> (lane & 32));
+        if (first) qpins[b + __popc(m & ((1u << l) - 1u))] = x;
+        uint64_t sum = first ? fp_term(x, 0) : 0ull;
+#pragma unroll
+        for (int o = 16; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+        if (l == 0) {
+            const int32_t len = __popc(m);
+            qlen[h] = len >= 2 ? len : 0;
+            fp[h] = fp_finish(sum, len);
         }
     }
-    qlen[e] = len >= 2 ? len : 0;
-    fp[e] = fp_finish(sum, len);
 }
 
 // Ascending bitonic sort of 64*R keys held R per lane (key i = lane*R + t),
@@ -346,7 +364,7 @@ __device__ __forceinline__ int32_t wave_unique_emit(const int32_t (&x)[R], int32
     return len;
 }
 
-// Degree 17..256: one wavefront per hyperedge, parents sorted in registers
+// Degree 33..256: one wavefront per hyperedge, parents sorted in registers
 // (block vb of that sweep).
 __device__ __forceinline__ void qbuild_wave(int64_t vb, int32_t count, const int32_t *list, const int32_t *off,
                                             const int32_t *pins, const int32_t *hseg, const uint8_t *sact,
@@ -357,7 +375,7 @@ __device__ __forceinline__ void qbuild_wave(int64_t vb, int32_t count, const int
     if (w >= count) return;
     int32_t e = list[w];
     int32_t b = off[e], d = off[e + 1] - b;
-    if (d <= kQbuildThreadMax) return;  // the one-thread sweep took it
+    if (d <= kQbuildThreadMax) return;  // the other blocks take it
     if (!sact[hseg[e]]) {
         if (lane == 0) qlen[e] = 0;
         return;
@@ -385,8 +403,8 @@ __device__ __forceinline__ void qbuild_wave(int64_t vb, int32_t count, const int
     }
 }
 
-// Both sweeps in one launch: blocks [0, ceil(E / kBlock)) one thread per
-// hyperedge, the rest one wavefront per listed mid hyperedge.
+// Both in one launch: blocks [0, ceil(E / kBlock)) the hyperedges of up to
+// kQbuildThreadMax pins, the rest one wavefront per listed larger one.
 __global__ __launch_bounds__(kBlock) void k_qbuild_sw(int32_t E, int32_t nmid, const int32_t *lmid,
                                                       const int32_t *off, const int32_t *pins,
                                                       const int32_t *hseg, const uint8_t *sact,

@@ -18,8 +18,7 @@ namespace bp {
 
 constexpr int kBlock = 256;           // threads per workgroup for sweeps
 constexpr int kWave = 64;             // CDNA wavefront
-constexpr int kSmallMax = 8;          // hyperedges up to this degree: one thread each
-constexpr int kMidMax = 256;          // up to this degree: one wavefront each
+constexpr int kMidMax = 256;          // listed hyperedges up to this degree: one wavefront each
 constexpr int kBigMax = 8192;         // up to this degree: one workgroup, sorted in LDS
 constexpr uint64_t kNoKey = ~0ull;
 

@@ -149,7 +149,7 @@ __device__ __forceinline__ void classify_block(int64_t vb, int32_t E, const int3
         int64_t e = first + r * kBlock + threadIdx.x;
         int32_t d = 0;
         if (e < E) d = (e + 1 < E ? off[e + 1] : P) - off[e];
-        lds_append(d > kSmallMax && d <= kMidMax, (int32_t)e, items[0], &cnt[0]);
+        lds_append(d > kHedgeThreadMax && d <= kMidMax, (int32_t)e, items[0], &cnt[0]);
         lds_append(d > kMidMax, (int32_t)e, items[1], &cnt[1]);
         lds_append(d > kBigMax, (int32_t)e, items[2], &cnt[2]);
     }

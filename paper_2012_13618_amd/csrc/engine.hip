@@ -493,13 +493,11 @@ void run_select(Ctx &cx, Level &L, Segs &sg, const int32_t *gain, const int32_t 
 
 static void flip(Ctx &cx, Level &L, Segs &sg, const int32_t *gain, const int32_t *go);
 
-// Whether a level's selections run in one workgroup per segment (kind 0:
-// flips, kind 1: balance); that kernel computes its lists' sizes and gain
+// Whether a level's selections run in one workgroup per segment; that kernel computes its lists' sizes and gain
 // extremes itself, so the gain passes need not.
-static bool seg_path(const Ctx &cx, const Level &L, int kind)
+static bool seg_path(const Ctx &cx, const Level &L)
 {
-    int32_t cap = kind == 0 ? seg_select_max<0, kSegThreads>() : seg_select_max<1, kSegThreads>();
-    return L.maxseg_nodes <= std::min(cx.sched.seg_select_max_nodes, cap);
+    return L.maxseg_nodes <= std::min(cx.sched.seg_select_max_nodes, kSegSelectMax);
 }
 
 // Whether a level's balance selections are windowed (window.hpp): segments too
@@ -508,7 +506,7 @@ static bool seg_path(const Ctx &cx, const Level &L, int kind)
 static bool win_path(const Ctx &cx, const Level &L)
 {
     const int32_t lim = cx.sched.chunk_select_max_nodes;
-    return !seg_path(cx, L, 1) && lim > 0 && (lim >= kChunkSelectCap || L.maxseg_nodes <= lim);
+    return !seg_path(cx, L) && lim > 0 && (lim >= kChunkSelectCap || L.maxseg_nodes <= lim);
 }
 
 // Buffers of the windowed selections of n levels (none when no level has one).
@@ -536,22 +534,28 @@ static void alloc_win(Ctx &cx, Segs &sg, const Level *lv, int32_t n)
     Fills().add(w.top + 3 * S, S, kWinStart).add(w.shift + 3 * S, S, 0).run(cx.lc);
 }
 
+// One workgroup per segment, of the size that the largest one needs.
+template <int KIND>
+static void launch_seg_select(Ctx &cx, Level &L, Segs &sg, const int32_t *gain, const BalFinish &bf, const int32_t *go)
+{
+    auto run = [&](auto kernel, int threads) {
+        launch(cx.lc, "seg_select", 6.0 * L.N, kernel, L.S, threads, 0, L.S, sel_view(L, sg, gain), sg.st, id_bits(L),
+               (const int32_t *)L.nw, (unsigned long long *)sg.w, bf, go);
+    };
+    if (L.maxseg_nodes <= 2048) run(&k_seg_select<KIND, 256, 8>, 256);
+    else if (L.maxseg_nodes <= 8192) run(&k_seg_select<KIND, 512, 16>, 512);
+    else run(&k_seg_select<KIND, 1024, 16>, 1024);
+}
+
 // Selection and flip of the chosen nodes (Algorithm 3 rounds, Algorithm 5
 // swaps): one workgroup per segment when every segment is small, else the
 // multi-workgroup passes and a flip launch.
 static void select_and_flip(Ctx &cx, Level &L, Segs &sg, const int32_t *gain, const int32_t *go)
 {
-    if (seg_path(cx, L, 0)) {
+    if (seg_path(cx, L)) {
         BalFinish bf{};
         bf.side = L.side;
-        if (L.maxseg_nodes <= seg_select_max<0, kSegThreadsSmall>())
-            launch(cx.lc, "seg_select", 6.0 * L.N, k_seg_select<0, kSegThreadsSmall>, L.S, kSegThreadsSmall, 0,
-                   L.S, sel_view(L, sg, gain), sg.st, id_bits(L), (const int32_t *)L.nw, (unsigned long long *)sg.w,
-                   bf, go);
-        else
-            launch(cx.lc, "seg_select", 6.0 * L.N, k_seg_select<0, kSegThreads>, L.S, kSegThreads, 0, L.S,
-                   sel_view(L, sg, gain), sg.st, id_bits(L), (const int32_t *)L.nw, (unsigned long long *)sg.w,
-                   bf, go);
+        launch_seg_select<0>(cx, L, sg, gain, bf, go);
         return;
     }
     run_select(cx, L, sg, gain, go);
@@ -738,7 +742,7 @@ static int64_t initial_rounds(Ctx &cx, Level &L, Segs &sg, int32_t j, int32_t *g
                (const int32_t *)sg.coarsest, (const int32_t *)sg.k0, (const int32_t *)sg.k1,
                (const int64_t *)sg.W, (const unsigned long long *)sg.w, sg.cnt1, ri, sg.mode, sg.gmask, sg.m,
                sg.st, sg.go);
-        run_gains(cx, L, sg, gain, !seg_path(cx, L, 0), gc);
+        run_gains(cx, L, sg, gain, !seg_path(cx, L), gc);
         select_and_flip(cx, L, sg, gain, gc);
     }, [] {});
 }
@@ -750,10 +754,10 @@ static int64_t refine_level(Ctx &cx, Level &L, Segs &sg, int32_t j, int32_t *gai
     for (int it = 0; it < cx.prm.refine_iters; it++) {
         // a later iteration finds the modes and masks the first one set, unless
         // the multi-workgroup selection needs its lists reset
-        if (it == 0 || !seg_path(cx, L, 0))
+        if (it == 0 || !seg_path(cx, L))
             launch(lc, "round", 0.0, k_round_refine, gs, kBlock, 0, L.S, j, (const int32_t *)sg.coarsest,
                    sg.mode, sg.gmask, sg.done, sg.st, sg.go);
-        run_gains(cx, L, sg, gain, !seg_path(cx, L, 0), nullptr);
+        run_gains(cx, L, sg, gain, !seg_path(cx, L), nullptr);
         select_and_flip(cx, L, sg, gain, nullptr);
     }
     if (cx.prm.refine_iters == 0)
@@ -829,7 +833,7 @@ static int64_t refine_level(Ctx &cx, Level &L, Segs &sg, int32_t j, int32_t *gai
     // (a windowed round may only move its window, a few times for each that moves nodes)
     const int64_t limit = ((int64_t)L.N + L.S + 2) * (win ? 16 : 1);
     int64_t rounds = chunked_rounds(cx, sg, limit, true, [&](int32_t ri, const int32_t *gc) {
-        bool seg = seg_path(cx, L, 1);
+        bool seg = seg_path(cx, L);
         if (ri == 0 || !incr) {
             launch(lc, "round", 0.0, k_round_balance, gs, kBlock, 0, rb, sg.st, sg.go, ri);
             run_gains(cx, L, sg, gain, !seg && !win, gc, incr);
@@ -851,18 +855,7 @@ static int64_t refine_level(Ctx &cx, Level &L, Segs &sg, int32_t j, int32_t *gai
                    ml.count, gc);
         }
         if (seg) {
-            if (L.maxseg_nodes <= seg_select_max<1, kSegThreadsSmall>())
-                launch(lc, "seg_select", 6.0 * L.N, k_seg_select<1, kSegThreadsSmall>, L.S, kSegThreadsSmall, 0,
-                       L.S, sel_view(L, sg, gain), sg.st, id_bits(L), (const int32_t *)L.nw,
-                       (unsigned long long *)sg.w, bf, gc);
-            else if (L.maxseg_nodes <= seg_select_max<1, kSegThreadsBal>())
-                launch(lc, "seg_select", 6.0 * L.N, k_seg_select<1, kSegThreadsBal>, L.S, kSegThreadsBal, 0, L.S,
-                       sel_view(L, sg, gain), sg.st, id_bits(L), (const int32_t *)L.nw,
-                       (unsigned long long *)sg.w, bf, gc);
-            else
-                launch(lc, "seg_select", 6.0 * L.N, k_seg_select<1, kSegThreads>, L.S, kSegThreads, 0, L.S,
-                       sel_view(L, sg, gain), sg.st, id_bits(L), (const int32_t *)L.nw,
-                       (unsigned long long *)sg.w, bf, gc);
+            launch_seg_select<1>(cx, L, sg, gain, bf, gc);
             return;
         }
         if (win) {

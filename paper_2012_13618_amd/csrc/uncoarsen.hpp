@@ -1043,17 +1043,17 @@ __device__ __forceinline__ bool sel_chosen(int64_t v, const SelView &sv, const S
 
 // ---- small segments: the whole selection and the moves in one workgroup --------------------
 
-constexpr int kSegThreads = 1024;     // flips above 4 K nodes
-constexpr int kSegThreadsBal = 768;   // balance from 8 K to 24 K nodes
-constexpr int kSegThreadsSmall = 256; // flips up to 4 K nodes, balance up to 8 K
-// nodes per thread, kept in registers: the flipping kind holds both lists'
-// thresholds as well.  1024 threads leave 128 registers per thread, 768
-// threads 170: 32 balance nodes each without spilling
-template <int KIND, int TH> constexpr int seg_items() { return KIND == 0 ? 16 : 32; }
-template <int KIND, int TH> constexpr int32_t seg_select_max() { return TH * seg_items<KIND, TH>(); }
-constexpr int kSegKeys = 256;                           // balance candidates: ceil(sqrt n) <= 182
+// Workgroups of a selection: threads, and nodes per thread, kept in registers
+// (the flipping kind holds both lists' thresholds as well; past 128 registers a
+// thread a workgroup of 1024 would spill).  The smallest that holds the level's
+// largest segment: items past a segment's end cost loads and compares all the
+// same (balance on up to 2048 nodes: 256 threads of 32 nodes 13 us, of 8 10.7;
+// up to 8192: 256 of 32 18.9 us, 512 of 16 15.0, 1024 of 8 15.1; up to 16384:
+// 768 of 32 19.6, 1024 of 16 16.4).
+constexpr int32_t kSegSelectMax = 16384;
+constexpr int kSegKeys = 128;  // balance candidates: ceil(sqrt(kSegSelectMax))
 
-// One workgroup per segment of at most seg_select_max<KIND, TH>() nodes: each list's
+// One workgroup per segment of at most TH * ITEMS nodes: each list's
 // r-th key by the same 12-bit radix select as the multi-workgroup passes,
 // with the segment's gains in registers and the histogram in LDS, then the
 // moves (bf.side is written): kind 0 flips the chosen nodes of both lists
@@ -1062,13 +1062,13 @@ constexpr int kSegKeys = 256;                           // balance candidates: c
 // gathered meanwhile) and the workgroup takes the balance prefix (Algorithm
 // 5).  The chosen set is the one the multi-workgroup path chooses: the same
 // keys, the same r.
-template <int KIND, int TH>
+template <int KIND, int TH, int ITEMS>
 __global__ __launch_bounds__(TH) void k_seg_select(int32_t S, SelView sv, SelState st, int idbits_lv,
                                                            const int32_t *nw,
                                                            unsigned long long *segw, BalFinish bf,
                                                            const int32_t *go)
 {
-    constexpr int kSegItems = seg_items<KIND, TH>();
+    constexpr int kSegItems = ITEMS;
     constexpr int32_t kCap = TH * kSegItems;
     constexpr int kKeys = kSegKeys;
     __shared__ uint32_t hist[kBins];

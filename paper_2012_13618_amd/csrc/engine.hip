@@ -79,8 +79,7 @@ void coarsen_level(Ctx &cx, Level &f, Segs &sg, uint8_t *&sact, uint8_t *&sact_n
     int64_t T = 1024;
     while (T < 2 * (int64_t)E) T <<= 1;
     b.tmask = (int32_t)(T - 1);
-    b.tkeys = ar.get<uint64_t>(T);
-    b.tmin = ar.get<int32_t>(T);
+    b.slots = ar.get<uint64_t>(T);
     b.counters = ar.get<int32_t>(8);
     b.totN = ar.get<int32_t>(1);
     b.totEP = ar.get<uint64_t>(1);
@@ -104,9 +103,9 @@ void coarsen_level(Ctx &cx, Level &f, Segs &sg, uint8_t *&sact, uint8_t *&sact_n
     uint64_t *hkey = ar.get<uint64_t>(E);
     HedgeKeyArgs hk{(const int32_t *)f.off, (const int32_t *)f.hw, (const int32_t *)f.hseg,
                     (const int32_t *)f.hbase, sact, cx.prm.policy, hkey};
-    launch(lc, "coarsen_init", 8.0 * N + 16.0 * E + 12.0 * T + 20.0 * E, k_coarsen_init,
+    launch(lc, "coarsen_init", 8.0 * N + 16.0 * E + 8.0 * T + 20.0 * E, k_coarsen_init,
            std::min<int64_t>(ceil_div(initn, kBlock), 8192), kBlock, 0, N, E, T, b.key, b.grp,
-           c.nw, b.cg, b.lead, b.wsum, b.tkeys, b.tmin, b.counters, hk);
+           c.nw, b.cg, b.lead, b.wsum, b.slots, b.counters, hk);
 
     // Algorithm 1: per-node minimum over its own hyperedges' keys
     run_match_keys(cx, f, sact, b.key, hkey);
@@ -165,10 +164,10 @@ void coarsen_level(Ctx &cx, Level &f, Segs &sg, uint8_t *&sact, uint8_t *&sact_n
     // duplicate pin sets
     launch(lc, "dedup", 16.0 * E, k_dd_insert, ceil_div(E, kBlock), kBlock, 0, E,
            (const int32_t *)b.qlen, (const uint64_t *)b.fp, (const int32_t *)b.rep, 0,
-           (unsigned long long *)b.tkeys, b.tmin, b.tmask, b.hslot);
+           (unsigned long long *)b.slots, b.tmask, b.hslot);
     launch(lc, "dedup", 20.0 * E, k_dd_resolve, ceil_div(E, kBlock), kBlock, 0, E,
            (const int32_t *)f.off, (const int32_t *)b.qpins, (const int32_t *)b.qlen,
-           (const int32_t *)f.hw, (const int32_t *)b.hslot, (const int32_t *)b.tmin, 0, b.rep,
+           (const int32_t *)f.hw, (const int32_t *)b.hslot, (const unsigned long long *)b.slots, 0, b.rep,
            b.wsum, b.counters);
 
     auto compact = [&]() {
@@ -212,18 +211,17 @@ void coarsen_level(Ctx &cx, Level &f, Segs &sg, uint8_t *&sact, uint8_t *&sact_n
         // a fingerprint shared by different pin sets: re-hash the open ones
         for (uint64_t salt = 1; inf.unresolved > 0; salt++) {
             if (salt > 64) throw Error(BP_ERR_DEVICE, "duplicate check did not converge");
-            fill(lc, b.tkeys, T, kEmptySlot);
-            fill(lc, b.tmin, T, INT32_MAX);
+            fill(lc, b.slots, T, kEmptySlot);
             fill(lc, b.counters, 8, 0);
             launch(lc, "dedup", 0.0, k_refingerprint, ceil_div(E, kBlock), kBlock, 0, E,
                    (const int32_t *)f.off, (const int32_t *)b.qpins, (const int32_t *)b.qlen,
                    (const int32_t *)b.rep, salt * 0x9E3779B97F4A7C15ull, b.fp);
             launch(lc, "dedup", 0.0, k_dd_insert, ceil_div(E, kBlock), kBlock, 0, E,
                    (const int32_t *)b.qlen, (const uint64_t *)b.fp, (const int32_t *)b.rep, 1,
-                   (unsigned long long *)b.tkeys, b.tmin, b.tmask, b.hslot);
+                   (unsigned long long *)b.slots, b.tmask, b.hslot);
             launch(lc, "dedup", 0.0, k_dd_resolve, ceil_div(E, kBlock), kBlock, 0, E,
                    (const int32_t *)f.off, (const int32_t *)b.qpins, (const int32_t *)b.qlen,
-                   (const int32_t *)f.hw, (const int32_t *)b.hslot, (const int32_t *)b.tmin, 1,
+                   (const int32_t *)f.hw, (const int32_t *)b.hslot, (const unsigned long long *)b.slots, 1,
                    b.rep, b.wsum, b.counters);
             launch(lc, "dedup", 0.0, k_level_fixup, 1, kFixupThreads, 0, S, N, E, (const int32_t *)f.nbase,
                    (const int32_t *)f.hbase, (const int32_t *)b.cid, (const int32_t *)b.hb_tmp,

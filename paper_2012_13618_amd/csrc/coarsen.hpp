@@ -578,8 +578,8 @@ __global__ void k_refingerprint(int32_t E, const int32_t *off, const int32_t *qp
 // smallest id of the hyperedges that have it, in one word, so that a hyperedge
 // without a duplicate costs one atomic and not two (atomics run at 27 G/s
 // wherever they go, which bounds this step: 8.2 M hyperedges 0.95 ms, now
-// 0.48).  Two sets that share those bits and a slot: about one level of 8 M
-// hyperedges in 2000, are told apart by the pin-by-pin check and hashed again.
+// 0.48).  Two sets that share those bits and a slot (about one level of 8 M
+// hyperedges in 2000) are told apart by the pin-by-pin check and hashed again.
 constexpr unsigned long long kDdId = 0x7fffffffull;
 __device__ __forceinline__ unsigned long long dd_word(unsigned long long f, int32_t e)
 {

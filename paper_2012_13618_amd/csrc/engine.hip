@@ -325,6 +325,14 @@ void run_match_keys(Ctx &cx, Level &L, const uint8_t *sact, uint64_t *key, const
                (const int32_t *)L.hbase, sact, cx.prm.policy, h);
         hkey = h;
     }
+    if (ml_ok(L)) {
+        if (!hkey_ready) fill(lc, key, L.N, kNoKey);  // (coarsen_init's part)
+        MatchLdsArgs a{L.E, ml_slabs(L), ceil_div(L.P, kRsTile), L.off, L.pins, L.hseg, L.nbase, L.hbase, L.tfirst,
+                       sact, hkey, (unsigned long long *)key};
+        launch3(lc, "match", 12.0 * L.E + 4.0 * L.P * ml_ranges(L) + 8.0 * L.N, k_match_lds,
+                dim3((unsigned)a.slabs, (unsigned)ml_ranges(L), 1), kMlThreads, 0, a);
+        return;
+    }
     double bytes = 8.0 * L.N + 4.0 * L.P + 8.0 * L.P + 8.0 * L.N;
     launch(lc, "match", bytes, k_match_sw, ceil_div(L.N, kBlock) + ceil_div(L.nmid_bound, kBlock / 64), kBlock, 0,
            L.N, (const int32_t *)L.ncount, (const int32_t *)L.lnmid, (const int32_t *)L.noff,

@@ -3,6 +3,7 @@
 #include "batch.hpp"
 #include "coarsen.hpp"
 #include "gain_lds.hpp"
+#include "match_lds.hpp"
 #include "kway.hpp"
 #include "refine.hpp"
 #include "uncoarsen.hpp"

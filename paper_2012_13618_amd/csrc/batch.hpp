@@ -158,7 +158,7 @@ __global__ __launch_bounds__(kBlock) void k_cut_seg(int32_t count, const int32_t
             unsigned long long c = 0;
             int32_t g = -1;
             if (e < hi && thread_split<SMALL>(off[e + 1] - off[e])) {
-                int32_t lam = hedge_lambda<SMALL>((int32_t)e, 0, 1, off, pins, part, mask64, orl, lds);
+                int32_t lam = cut_lambda<1>(off[e], off[e + 1] - off[e], 0, pins, part, mask64, orl, lds);
                 if (lam > 1) {
                     c = (unsigned long long)hw[e] * (lam - 1);
                     g = hseg[e];
@@ -181,13 +181,13 @@ __global__ __launch_bounds__(kBlock) void k_cut_seg(int32_t count, const int32_t
         for (int64_t i = lo + (threadIdx.x >> 6); i < hi; i += blockDim.x >> 6) {
             int32_t e = list[i];
             if (!thread_split<WAVE>(off[e + 1] - off[e])) continue;
-            int32_t lam = hedge_lambda<WAVE>(e, threadIdx.x & 63, 64, off, pins, part, mask64, orl, lds);
+            int32_t lam = cut_lambda<64>(off[e], off[e + 1] - off[e], threadIdx.x & 63, pins, part, mask64, orl, lds);
             if ((threadIdx.x & 63) == 0 && lam > 1) add(e, lam);
         }
     } else {
         for (int64_t i = lo; i < hi; i++) {
             int32_t e = list[i];
-            int32_t lam = hedge_lambda<BLOCK>(e, threadIdx.x, blockDim.x, off, pins, part, mask64, orl, lds);
+            int32_t lam = cut_lambda<kBlock>(off[e], off[e + 1] - off[e], threadIdx.x, pins, part, mask64, orl, lds);
             if (threadIdx.x == 0 && lam > 1) add(e, lam);
         }
     }

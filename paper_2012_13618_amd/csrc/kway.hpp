@@ -16,42 +16,49 @@ struct ValidateOut {
     unsigned long long sum_nw, sum_hw;
 };
 
-__global__ __launch_bounds__(kBlock) void k_validate(int32_t N, int32_t E, const int32_t *off,
-                                                     const int32_t *pins, const int32_t *nw,
-                                                     const int32_t *hw, ValidateOut *out)
+// One workgroup a CU with eight pins a thread in flight: the sums end in one
+// atomic a workgroup and array, 11 ns each on one address (2048 workgroups of
+// 256 threads spent 45 of 59 us there at 5.4 M pins, now 16 in all).
+constexpr int kValThreads = 1024;
+__global__ __launch_bounds__(kValThreads) void k_validate(int32_t N, int32_t E, const int32_t *off,
+                                                          const int32_t *pins, const int32_t *nw,
+                                                          const int32_t *hw, ValidateOut *out)
 {
     __shared__ int64_t lds[16];
-    int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    int64_t P = off[E];
+    const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    const int64_t P = off[E];
     int64_t snw = 0, shw = 0;
     int bo = 0, bp_ = 0, bw = 0;
+#pragma unroll 4
     for (int64_t e = tid; e < E; e += stride) {
+        const int32_t w = hw ? hw[e] : 0;
         if (off[e + 1] < off[e]) bo = 1;
-        if (hw) {
-            if (hw[e] < 0) bw = 1;
-            shw += hw[e];
-        }
+        if (w < 0) bw = 1;
+        shw += w;
     }
     if (tid == 0 && (off[0] != 0 || P < 0)) bo = 1;
-    for (int64_t i = tid; i < P && !bo; i += stride) {
-        int32_t v = pins[i];
-        if (v < 0 || v >= N) bp_ = 1;
+    if (!bo) {
+#pragma unroll 8
+        for (int64_t i = tid; i < P; i += stride)
+            if ((uint32_t)pins[i] >= (uint32_t)N) bp_ = 1;
     }
-    for (int64_t v = tid; v < N; v += stride) {
-        if (nw) {
-            if (nw[v] < 0) bw = 1;
-            snw += nw[v];
+    if (nw) {
+#pragma unroll 4
+        for (int64_t v = tid; v < N; v += stride) {
+            const int32_t w = nw[v];
+            if (w < 0) bw = 1;
+            snw += w;
         }
     }
-    snw = block_sum(snw, lds);
-    shw = block_sum(shw, lds);
     if (bo) atomicOr(&out->bad_offsets, 1);
     if (bp_) atomicOr(&out->bad_pins, 1);
     if (bw) atomicOr(&out->bad_weights, 1);
+    if (nw) snw = block_sum(snw, lds);
+    if (hw) shw = block_sum(shw, lds);
     if (threadIdx.x == 0) {
-        atomicAdd(&out->sum_nw, (unsigned long long)snw);
-        atomicAdd(&out->sum_hw, (unsigned long long)shw);
+        if (nw) atomicAdd(&out->sum_nw, (unsigned long long)snw);
+        if (hw) atomicAdd(&out->sum_hw, (unsigned long long)shw);
     }
 }
 
@@ -335,115 +342,159 @@ __global__ __launch_bounds__(kBlock) void k_extract_hedges(
 
 // ---- connectivity-1 cut of the final partition ----------------------------------
 
-// Connectivity (number of distinct parts) of hyperedge e, computed by its
-// schedule group: a part bitmask when every part id is below 64, else a
-// count of parts not seen at an earlier pin (O(d^2), rare large hyperedges).
-template <int S>
-__device__ __forceinline__ int32_t hedge_lambda(int32_t e, int lane, int stride, const int32_t *off,
-                                                const int32_t *pins, const int32_t *part, bool mask64,
-                                                unsigned long long *orl, int32_t *lds)
+// Connectivity (number of distinct parts) of a hyperedge by lanes lane, lane +
+// STRIDE, ... (1: a thread alone, 64: a wavefront, else the workgroup): a part
+// bitmask when every part id is below 64, else a count of parts not seen at an
+// earlier pin (O(d^2), rare large hyperedges).
+template <int STRIDE, typename PART>
+__device__ __forceinline__ int32_t cut_lambda(int32_t b, int32_t d, int lane, const int32_t *pins, const PART *part,
+                                              bool mask64, unsigned long long *orl, int32_t *lds)
 {
-    int32_t b = off[e], d = off[e + 1] - b;
+    constexpr int R = 8;
     if (mask64) {
         unsigned long long m = 0;
-        for (int i = lane; i < d; i += stride) m |= 1ull << (part[pins[b + i]] & 63);
-        if (S != SMALL) {
+        for (int32_t i0 = lane; i0 < d; i0 += R * STRIDE) {
+            int32_t v[R];
+            PART p[R];
+#pragma unroll
+            for (int j = 0; j < R; j++) v[j] = pins[b + min(i0 + j * STRIDE, d - 1)];
+#pragma unroll
+            for (int j = 0; j < R; j++) p[j] = part[v[j]];
+#pragma unroll
+            for (int j = 0; j < R; j++) m |= 1ull << (p[j] & 63);
+        }
+        if (STRIDE > 1)
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) m |= __shfl_xor(m, o, 64);
-        }
-        if (S == BLOCK) {
+        if (STRIDE > 64) {
+            __syncthreads();
             if ((threadIdx.x & 63) == 0) orl[threadIdx.x >> 6] = m;
             __syncthreads();
             m = 0;
-            for (int i = 0; i < (int)(blockDim.x >> 6); i++) m |= orl[i];
-            __syncthreads();
+            for (int i = 0; i < STRIDE / 64; i++) m |= orl[i];
         }
         return __popcll(m);
     }
     int32_t lam = 0;
-    for (int i = lane; i < d; i += stride) {
-        int32_t p = part[pins[b + i]];
+    for (int32_t i = lane; i < d; i += STRIDE) {
+        const int32_t p = part[pins[b + i]];
         bool first = true;
-        for (int j = 0; j < i && first; j++) first = part[pins[b + j]] != p;
+        for (int32_t j = 0; j < i && first; j++) first = part[pins[b + j]] != p;
         lam += first ? 1 : 0;
     }
-    return group_sum<S>(lam, lds);
+    if (STRIDE == 64) lam = wave_sum(lam);
+    if (STRIDE > 64) lam = block_sum(lam, lds);
+    return lam;
 }
 
-// Connectivity-1 cut, summed over the hyperedges of one schedule (SMALL: all
-// hyperedges of degree <= 8, one per thread; WAVE / BLOCK: the listed ones).
-// Each workgroup writes its sum to partial[blockIdx.x] (no same-address
-// atomics); k_sum_u64 adds the partial sums up.  SMALL: contiguous chunks of
-// about two hyperedges a thread (at most kCutBlocks workgroups); WAVE / BLOCK: the listed
-// hyperedges, as many workgroups as keep every wavefront on about one
-// hyperedge (at most kCutBlocks).
+// Launch sizes of the batch's cut (k_cut_seg).  SMALL: contiguous chunks of
+// about two hyperedges a thread; WAVE: the listed hyperedges, one a wavefront
+// (at most kCutBlocks workgroups).
 constexpr int64_t kCutBlocks = 16384;
 
 template <int S> inline int64_t cut_grid(int64_t count)
 {
-    if (S == SMALL) {  // two hyperedges a thread: enough loads in flight to cover the gathers
-        int64_t g = ceil_div(count, (int64_t)2 * kBlock);
-        return g < kCutBlocks ? g : kCutBlocks;
-    }
-    int64_t g = S == WAVE ? sched_grid<WAVE>(count) : count;
+    int64_t g = S == SMALL ? ceil_div(count, (int64_t)2 * kBlock) : sched_grid<WAVE>(count);
     return g < kCutBlocks ? g : kCutBlocks;
 }
 
-template <int S>
-__global__ __launch_bounds__(kBlock) void k_cut(int32_t count, const int32_t *list, const int32_t *off,
-                                                const int32_t *pins, const int32_t *hw, const int32_t *part,
-                                                int mask64, unsigned long long *partial)
+// Connectivity-1 cut of all hyperedges, added to acc[0], and the largest of the
+// k part weights pw, to acc[1].  A workgroup takes tiles of kCutThreads
+// hyperedges: those of up to kHedgeThreadMax pins a thread each, with eight
+// gathers in flight; larger ones are queued and taken by wavefronts, and from
+// kCutHuge pins by the whole workgroup.  One barrier a tile: queue and counter
+// of a tile are not those of the next.
+//
+// The gathers of the pins' parts bound it, so they are bytes where the parts of
+// a level would not stay in the L2s (PART uint8_t).  5.4 M pins over 1 M nodes:
+// three launches by lists 82 us, and the lists' 12 and a readback; now 58 by
+// ints and 47 by bytes.  115 M pins over 10 M nodes: 2.73 ms, now 1.34.  Four
+// gathers in flight: 43 us and 1.45 ms.
+// ok: nothing is read through the pins if it says that they are not valid.
+constexpr int kCutThreads = 512;
+constexpr int kCutMaxBlocks = 1024;  // (512 threads: two waves' worth of them fill the card)
+constexpr int32_t kCutHuge = 4096;
+constexpr int kCutHugeQueue = 64;
+
+template <typename PART>
+__global__ __launch_bounds__(kCutThreads) void k_cut(int32_t E, const int32_t *off, const int32_t *pins,
+                                                     const int32_t *hw, const PART *part, int mask64, int32_t k,
+                                                     const unsigned long long *pw, unsigned long long *acc,
+                                                     const ValidateOut *ok)
 {
+    __shared__ int32_t queue[2][kCutThreads], huge[2][kCutHugeQueue];
+    __shared__ int32_t nq[3], nh[3];
     __shared__ unsigned long long orl[16];
     __shared__ int32_t lds[16];
     __shared__ int64_t lds64[16];
+    if (ok && (ok->bad_offsets || ok->bad_pins)) return;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    if (blockIdx.x == 0) {
+        unsigned long long m = 0;
+        for (int32_t i = tid; i < k; i += kCutThreads) m = pw[i] > m ? pw[i] : m;
+        m = wave_max(m);
+        if (lane == 0 && m) atomicMax(&acc[1], m);
+    }
+    if (tid < 3) {
+        nq[tid] = 0;
+        nh[tid] = 0;
+    }
+    __syncthreads();
     int64_t contrib = 0;
-    if (S == SMALL) {
-        for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < count;
-             e += (int64_t)gridDim.x * blockDim.x) {
-            if (!thread_split<SMALL>(off[e + 1] - off[e])) continue;
-            int32_t lam = hedge_lambda<SMALL>((int32_t)e, 0, 1, off, pins, part, mask64, orl, lds);
-            if (lam > 1) contrib += (int64_t)(hw ? hw[e] : 1) * (lam - 1);
+    int t = 0, t3 = 0;
+    for (int64_t e0 = (int64_t)blockIdx.x * kCutThreads; e0 < E; e0 += (int64_t)gridDim.x * kCutThreads) {
+        const int32_t e = (int32_t)(e0 + tid);
+        if (e < E) {
+            const int32_t b = off[e], d = off[e + 1] - b;
+            int32_t h = kCutHugeQueue;
+            if (d >= kCutHuge) {
+                h = atomicAdd(&nh[t3], 1);
+                if (h < kCutHugeQueue) huge[t][h] = e;
+            }
+            if (d <= kHedgeThreadMax) {
+                if (d >= 2) {
+                    const int32_t lam = cut_lambda<1>(b, d, 0, pins, part, mask64, orl, lds);
+                    if (lam > 1) contrib += (int64_t)(hw ? hw[e] : 1) * (lam - 1);
+                }
+            } else if (h >= kCutHugeQueue) {
+                queue[t][atomicAdd(&nq[t3], 1)] = e;
+            }
         }
-    } else if (S == WAVE) {
-        int64_t wpb = blockDim.x >> 6;
-        for (int64_t i = (int64_t)blockIdx.x * wpb + (threadIdx.x >> 6); i < count; i += (int64_t)gridDim.x * wpb) {
-            int32_t e = list[i];
-            if (!thread_split<WAVE>(off[e + 1] - off[e])) continue;
-            int32_t lam = hedge_lambda<WAVE>(e, threadIdx.x & 63, 64, off, pins, part, mask64, orl, lds);
-            if ((threadIdx.x & 63) == 0 && lam > 1) contrib += (int64_t)(hw ? hw[e] : 1) * (lam - 1);
+        __syncthreads();
+        const int32_t n = nq[t3], m = min(nh[t3], kCutHugeQueue), free3 = t3 == 0 ? 2 : t3 - 1;
+        if (tid == 0) {  // (the counters of the tile after the next, last read before this barrier)
+            nq[free3] = 0;
+            nh[free3] = 0;
         }
-    } else {
-        for (int64_t i = blockIdx.x; i < count; i += gridDim.x) {
-            int32_t e = list[i];
-            int32_t lam = hedge_lambda<BLOCK>(e, threadIdx.x, blockDim.x, off, pins, part, mask64, orl, lds);
-            if (threadIdx.x == 0 && lam > 1) contrib += (int64_t)(hw ? hw[e] : 1) * (lam - 1);
+        for (int32_t q = wv; q < n; q += kCutThreads / 64) {
+            const int32_t x = queue[t][q], b = off[x];
+            const int32_t lam = cut_lambda<64>(b, off[x + 1] - b, lane, pins, part, mask64, orl, lds);
+            if (lane == 0 && lam > 1) contrib += (int64_t)(hw ? hw[x] : 1) * (lam - 1);
         }
+        for (int32_t q = 0; q < m; q++) {
+            const int32_t x = huge[t][q], b = off[x];
+            const int32_t lam = cut_lambda<kCutThreads>(b, off[x + 1] - b, tid, pins, part, mask64, orl, lds);
+            if (tid == 0 && lam > 1) contrib += (int64_t)(hw ? hw[x] : 1) * (lam - 1);
+        }
+        t ^= 1;
+        t3 = t3 == 2 ? 0 : t3 + 1;
     }
     contrib = block_sum(contrib, lds64);
-    if (threadIdx.x == 0) partial[blockIdx.x] = (unsigned long long)contrib;
+    if (tid == 0 && contrib) atomicAdd(&acc[0], (unsigned long long)contrib);
 }
 
-// out[0] = the sum of a[0, n): one workgroup.
-__global__ void k_sum_u64(int32_t n, const unsigned long long *a, unsigned long long *out)
+// Workgroups of k_cut: as many as give each the same number of tiles.
+inline int64_t cut_blocks(int64_t E)
 {
-    __shared__ unsigned long long lds[16];
-    unsigned long long t = 0;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) t += a[i];
-    t = wave_sum(t);
-    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = t;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned long long r = 0;
-        for (int i = 0; i < (int)(blockDim.x >> 6); i++) r += lds[i];
-        *out = r;
-    }
+    const int64_t tiles = std::max<int64_t>(ceil_div(E, kCutThreads), 1);
+    return ceil_div(tiles, ceil_div(tiles, kCutMaxBlocks));
 }
 
 // Part weights: registers for k <= 8, an LDS histogram for k <= 4096, else
-// global atomics; one global atomic per part per workgroup otherwise.
+// global atomics; one global atomic per part per workgroup otherwise.  With
+// bytes also the parts' low bytes.
 __global__ __launch_bounds__(kBlock) void k_part_weights(int32_t N, int32_t k, const int32_t *part,
-                                                         const int32_t *nw,
+                                                         const int32_t *nw, uint8_t *bytes,
                                                          unsigned long long *pw)
 {
     __shared__ unsigned long long acc[4096];
@@ -454,6 +505,7 @@ __global__ __launch_bounds__(kBlock) void k_part_weights(int32_t N, int32_t k, c
         for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < N; v += stride) {
             int32_t p = part[v];
             int64_t w = nw ? nw[v] : 1;
+            if (bytes) bytes[v] = (uint8_t)p;
 #pragma unroll
             for (int j = 0; j < 8; j++) r[j] += p == j ? w : 0;
         }
@@ -471,6 +523,7 @@ __global__ __launch_bounds__(kBlock) void k_part_weights(int32_t N, int32_t k, c
     }
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < N; v += stride) {
         int32_t p = part[v];
+        if (bytes) bytes[v] = (uint8_t)p;
         if (p < 0 || p >= k) continue;  // range is the caller's contract; never write outside
         unsigned long long w = (unsigned long long)(nw ? nw[v] : 1);
         if (in_lds) atomicAdd(&acc[p], w);
@@ -480,21 +533,6 @@ __global__ __launch_bounds__(kBlock) void k_part_weights(int32_t N, int32_t k, c
         __syncthreads();
         for (int i = threadIdx.x; i < k; i += blockDim.x)
             if (acc[i]) atomicAdd(&pw[i], acc[i]);
-    }
-}
-
-__global__ void k_max_u64(int32_t n, const unsigned long long *a, unsigned long long *out)
-{
-    __shared__ unsigned long long lds[16];
-    unsigned long long m = 0;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) m = a[i] > m ? a[i] : m;
-    m = wave_max(m);
-    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned long long r = 0;
-        for (int i = 0; i < (int)(blockDim.x >> 6); i++) r = lds[i] > r ? lds[i] : r;
-        *out = r;
     }
 }
 

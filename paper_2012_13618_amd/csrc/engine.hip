@@ -1120,7 +1120,7 @@ static bool extract(Ctx &cx, TreeLevel &t, int32_t *d_part, TreeLevel &nx)
     ct.lo = ar.get<int32_t>(2 * S);
     ct.F = ar.get<uint64_t>(2 * S);
     cx.clear_info();
-    launch(lc, "extract", 0.0, k_child_table, 1, 1, 0, S, N, E, (const int32_t *)L.nbase,
+    launch(lc, "extract", 0.0, k_child_table, 1, kChildThreads, 0, S, N, E, (const int32_t *)L.nbase,
            (const int32_t *)L.hbase, (const int32_t *)t.sg.k0, (const int32_t *)t.sg.k1,
            (const int32_t *)t.sg.lo, (const uint64_t *)t.F, (const uint64_t *)nscan, (const uint64_t *)hs0,
            (const uint64_t *)hs1, (const uint64_t *)tots, (const uint64_t *)(tots + 1),

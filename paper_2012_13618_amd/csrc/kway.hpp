@@ -259,6 +259,17 @@ __global__ __launch_bounds__(kChildThreads) void k_child_table(
     info->active = c;
 }
 
+// Part ids of a tree level whose children are all single parts.
+__global__ __launch_bounds__(kBlock) void k_last_parts(int32_t N, const int32_t *nseg, const uint8_t *side,
+                                                       const int32_t *orig, const int32_t *k0, const int32_t *lo,
+                                                       int32_t *part)
+{
+    int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (v >= N) return;
+    const int32_t s = nseg[v];
+    part[orig[v]] = lo[s] + (side[v] ? k0[s] : 0);
+}
+
 // nodes: renumber into their child, or write the final part id
 __global__ __launch_bounds__(kBlock) void k_extract_nodes(
     int32_t N, const int32_t *nseg, const int32_t *nbase, const uint8_t *side,

@@ -255,19 +255,43 @@ void build_incidence(Ctx &cx, Level &L)
     LaunchCtx &lc = cx.lc;
     check_lists(L);
     const int32_t N = L.N, E = L.E, P = L.P;
-    uint32_t *k0 = ar.get<uint32_t>(P), *k1 = ar.get<uint32_t>(P);
-    int32_t *v0 = ar.get<int32_t>(P), *v1 = ar.get<int32_t>(P);
-    int bits = 0;
-    while (bits < 31 && ((int64_t)1 << bits) < (int64_t)N) bits++;
-    int64_t ntiles = ceil_div(P > 0 ? P : 1, kRsTile);
-    uint32_t *counts = L.counts0 ? L.counts0 : ar.get<uint32_t>(256 * ntiles), *offs = ar.get<uint32_t>(256 * ntiles);
-    uint32_t *tot = ar.get<uint32_t>(1);
+    const int64_t ntiles = ceil_div(P > 0 ? P : 1, kRsTile);
     if (!L.tfirst && P > 0) {
         L.tfirst = ar.get<int32_t>(ntiles);
         L.tnext = ar.get<int2>(4 * ntiles);
         launch(lc, "incidence", 4.0 * E, k_tile_starts, ceil_div(E, kBlock), kBlock, 0, E, ntiles,
                (const int32_t *)L.off, L.tfirst, L.tnext);
     }
+    L.noff = ar.get<int32_t>((int64_t)N + 1);
+    L.nmid_bound = std::min<int64_t>(N, P / (kNodeSmallMax + 1)) + 1;
+    L.nbig_bound = std::min<int64_t>(N, P / (kNodeMidMax + 1)) + 1;
+    L.lnmid = ar.get<int32_t>(L.nmid_bound);
+    L.lnbig = ar.get<int32_t>(L.nbig_bound);
+    L.ncount = ar.get<int32_t>(4);
+    L.bigslot = ar.get<int32_t>(N);
+    // no node has more incidences than pins, or on a coarse level (no pin twice
+    // in a hyperedge) than a segment has hyperedges
+    const bool none_big = P <= kNodeMidMax || (L.counts0 && L.maxseg_hedges <= kNodeMidMax);
+    L.nchunk_bound = none_big ? 0 : (int64_t)P / kNodeChunk + L.nbig_bound + 1;
+    L.chunk_node = ar.get<int32_t>(L.nchunk_bound + 1);
+    L.chunk_beg = ar.get<int32_t>(L.nchunk_bound + 1);
+    L.chunk_big = ar.get<int32_t>(L.nchunk_bound + 1);
+    L.big_chunks = ar.get<int32_t>(L.nbig_bound);
+    L.big_done = ar.get<int32_t>(L.nbig_bound);
+    L.cc = ar.get<int2>(E);
+    if (inc_one(L)) {
+        L.inc = ar.get<int32_t>(P);
+        IncOneArgs a{N, E, P, L.off, L.pins, L.noff, L.inc, L.lnmid, L.lnbig, L.ncount, L.bigslot, L.chunk_node,
+                     L.chunk_beg, L.chunk_big, L.big_chunks};
+        launch(lc, "incidence", 12.0 * P + 8.0 * N, k_incidence_one, 1, kIncOneThreads, 0, a);
+        return;
+    }
+    uint32_t *k0 = ar.get<uint32_t>(P), *k1 = ar.get<uint32_t>(P);
+    int32_t *v0 = ar.get<int32_t>(P), *v1 = ar.get<int32_t>(P);
+    int bits = 0;
+    while (bits < 31 && ((int64_t)1 << bits) < (int64_t)N) bits++;
+    uint32_t *counts = L.counts0 ? L.counts0 : ar.get<uint32_t>(256 * ntiles), *offs = ar.get<uint32_t>(256 * ntiles);
+    uint32_t *tot = ar.get<uint32_t>(1);
     // the first pass reads the keys (the pins) in place and finds the values
     // (their hyperedges) from off; it runs for a single node too
     const uint32_t *kin = (const uint32_t *)L.pins;
@@ -288,29 +312,16 @@ void build_incidence(Ctx &cx, Level &L)
         std::swap(v0, v1);
     }
     L.inc = v0;
-    L.noff = ar.get<int32_t>((int64_t)N + 1);
     // (kin: the sorted keys, or the pins themselves when no pass ran)
     launch(lc, "incidence", 4.0 * N, k_node_offsets, ceil_div((int64_t)N + 1, kBlock), kBlock, 0, kin,
            (int64_t)P, N, L.noff);
-    L.nmid_bound = std::min<int64_t>(N, P / (kNodeSmallMax + 1)) + 1;
-    L.nbig_bound = std::min<int64_t>(N, P / (kNodeMidMax + 1)) + 1;
-    L.lnmid = ar.get<int32_t>(L.nmid_bound);
-    L.lnbig = ar.get<int32_t>(L.nbig_bound);
-    L.ncount = ar.get<int32_t>(4);
-    L.bigslot = ar.get<int32_t>(N);
     Fills().add(L.ncount, 4, 0).add(L.bigslot, (int64_t)N, -1).run(lc);
     launch(lc, "incidence", 8.0 * N, k_classify_nodes, ceil_div(N, kClsNodes), kBlock, 0, N,
            (const int32_t *)L.noff, L.lnmid, L.lnbig, L.ncount);
-    L.nchunk_bound = (int64_t)P / kNodeChunk + L.nbig_bound + 1;
-    L.chunk_node = ar.get<int32_t>(L.nchunk_bound);
-    L.chunk_beg = ar.get<int32_t>(L.nchunk_bound);
-    L.chunk_big = ar.get<int32_t>(L.nchunk_bound);
-    L.big_chunks = ar.get<int32_t>(L.nbig_bound);
-    L.big_done = ar.get<int32_t>(L.nbig_bound);
+    if (none_big) return;
     launch(lc, "incidence", 0.0, k_big_chunks, 1, kBlock, 0, (const int32_t *)L.lnbig,
            (const int32_t *)L.noff, L.ncount, L.chunk_node, L.chunk_beg, L.chunk_big, L.big_chunks,
            L.bigslot);
-    L.cc = ar.get<int2>(E);
 }
 
 void run_match_keys(Ctx &cx, Level &L, const uint8_t *sact, uint64_t *key, const uint64_t *hkey_ready)

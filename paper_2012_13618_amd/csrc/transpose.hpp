@@ -261,6 +261,134 @@ __global__ __launch_bounds__(kBlock) void k_classify_nodes(int32_t N, const int3
     for (int i = threadIdx.x; i < cnt[1]; i += blockDim.x) lbig[base[1] + i] = items[1][i];
 }
 
+// The incidence of a small level with its node buckets and chunk table, by one
+// workgroup: degrees counted in LDS, a scan, then each pin's hyperedge placed by
+// its node's cursor (a node's hyperedges in no order; nothing asks for one).
+// The passes take up to eleven launches of about 5 us for it: a partition of
+// 1,000 nodes 858 us with them and 690 this way, of 12 K nodes 4.50 and 4.35 ms.
+// The lists are staged in LDS, as one store to 64 lines keeps a lone workgroup
+// from its next (some 30,000 pins 31 us straight to memory, 20 staged), so what
+// the LDS holds is the limit; a level at it takes 35 us, by the passes about 60.
+constexpr int kIncOneThreads = 1024;
+constexpr int32_t kIncOneWords = 36864;   // of LDS: a counter a node, 16 bits a pin
+constexpr int32_t kIncOneHedges = 16384;
+constexpr int kIncOneQueue = 1024;        // hyperedges taken by wavefronts
+
+struct IncOneArgs {
+    int32_t N, E, P;
+    const int32_t *off, *pins;
+    int32_t *noff, *inc, *lnmid, *lnbig, *ncount, *bigslot, *chunk_node, *chunk_beg, *chunk_big, *big_chunks;
+};
+
+template <int STRIDE>
+__device__ __forceinline__ void place_pins(int32_t e, int32_t b, int32_t d, int lane, const IncOneArgs &a, int32_t *cur,
+                                           uint16_t *to)
+{
+    constexpr int R = 8;
+    for (int32_t i0 = lane; i0 < d; i0 += R * STRIDE) {
+        int32_t u[R];
+#pragma unroll
+        for (int j = 0; j < R; j++) u[j] = a.pins[b + min(i0 + j * STRIDE, d - 1)];
+#pragma unroll
+        for (int j = 0; j < R; j++)
+            if (i0 + j * STRIDE < d && (uint32_t)u[j] < (uint32_t)a.N) to[atomicAdd(&cur[u[j]], 1)] = (uint16_t)e;
+    }
+}
+
+__global__ __launch_bounds__(kIncOneThreads) void k_incidence_one(IncOneArgs a)
+{
+    __shared__ int32_t buf[kIncOneWords], queue[kIncOneQueue], lds[16];
+    __shared__ int32_t nq, nmid, nbig, nchunk;
+    const int tid = threadIdx.x;
+    int32_t *cur = buf;                           // [N]
+    uint16_t *to = (uint16_t *)(buf + a.N);       // [P]
+    for (int32_t v = tid; v < a.N; v += kIncOneThreads) cur[v] = 0;
+    if (tid == 0) {
+        nq = 0;
+        nmid = 0;
+        nbig = 0;
+        nchunk = 0;
+    }
+    __syncthreads();
+    constexpr int R = 8;
+    for (int32_t i0 = tid; i0 < a.P; i0 += R * kIncOneThreads) {
+        int32_t u[R];
+#pragma unroll
+        for (int j = 0; j < R; j++) u[j] = a.pins[min(i0 + j * kIncOneThreads, a.P - 1)];
+#pragma unroll
+        for (int j = 0; j < R; j++)
+            if (i0 + j * kIncOneThreads < a.P && (uint32_t)u[j] < (uint32_t)a.N) atomicAdd(&cur[u[j]], 1);
+    }
+    __syncthreads();
+    const int32_t run = (a.N + kIncOneThreads - 1) / kIncOneThreads;
+    const int32_t v0 = tid * run, v1 = min(v0 + run, a.N);
+    int32_t sum = 0, tot;
+    for (int32_t v = v0; v < v1; v++) sum += cur[v];
+    int32_t at = block_excl_scan(sum, lds, &tot);
+    for (int32_t v = v0; v < v1; v++) {
+        const int32_t d = cur[v];
+        a.noff[v] = at;
+        cur[v] = at;
+        int32_t slot = -1;
+        if (d > kNodeMidMax) {
+            slot = atomicAdd(&nbig, 1);
+            const int32_t n = (int32_t)ceil_div(d, kNodeChunk), q = atomicAdd(&nchunk, n);
+            a.lnbig[slot] = v;
+            a.big_chunks[slot] = n;
+            for (int32_t j = 0; j < n; j++) {
+                a.chunk_node[q + j] = v;
+                a.chunk_beg[q + j] = at + j * kNodeChunk;
+                a.chunk_big[q + j] = slot;
+            }
+        } else if (d > kNodeSmallMax) {
+            a.lnmid[atomicAdd(&nmid, 1)] = v;
+        }
+        a.bigslot[v] = slot;
+        at += d;
+    }
+    if (tid == 0) a.noff[a.N] = tot;
+    __syncthreads();
+    int32_t nb = 0, ne = 0;
+    if (tid < a.E) {
+        nb = a.off[tid];
+        ne = a.off[tid + 1];
+    }
+    for (int32_t e = tid; e < a.E; e += kIncOneThreads) {
+        const int32_t b = nb, d = ne - nb;
+        if (e + kIncOneThreads < a.E) {
+            nb = a.off[e + kIncOneThreads];
+            ne = a.off[e + kIncOneThreads + 1];
+        }
+        if (d > kHedgeThreadMax) {
+            const int32_t q = atomicAdd(&nq, 1);
+            if (q < kIncOneQueue) {
+                queue[q] = e;
+                continue;
+            }
+        }
+        place_pins<1>(e, b, d, 0, a, cur, to);
+    }
+    if (tid == 0) {
+        a.ncount[0] = nmid;
+        a.ncount[1] = nbig;
+        a.ncount[2] = nchunk;
+        a.ncount[3] = 0;
+    }
+    __syncthreads();
+    for (int32_t q = tid >> 6; q < min(nq, kIncOneQueue); q += kIncOneThreads / 64) {
+        const int32_t e = queue[q], b = a.off[e];
+        place_pins<64>(e, b, a.off[e + 1] - b, tid & 63, a, cur, to);
+    }
+    __syncthreads();
+    for (int32_t i = tid; i < tot; i += kIncOneThreads) a.inc[i] = to[i];
+}
+
+inline bool inc_one(const Level &L)
+{
+    static_assert(kIncOneHedges <= 65536, "hyperedges are staged in 16 bits");
+    return L.E <= kIncOneHedges && (int64_t)L.N + (L.P + 1) / 2 <= kIncOneWords;
+}
+
 // Chunk table of the big nodes: one workgroup walks them in tiles of 256 and
 // places each node's chunks after a prefix sum of the chunk counts.
 __global__ __launch_bounds__(kBlock) void k_big_chunks(const int32_t *lnbig, const int32_t *noff,

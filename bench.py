@@ -151,7 +151,7 @@ def cpu_baseline(name, h, k, eps, budget_s):
 # hardware-counter summaries, which name device functions).
 FAMILY_KERNEL = {"gain_nodes": "k_gain_nodes", "gain_hedges": "k_gain_hedges", "select": "k_select_pass",
                  "seg_select": "k_seg_select", "gain_update": "k_gain_update", "seg_balance": "k_seg_fused",
-                 "win_hist": "k_win_hist", "win_take": "k_win_take",
+                 "win_hist": "k_win_hist", "win_take": "k_win_take", "gain_lds": "k_gain_lds",
                  "seg_initial": "k_seg_fused"}
 
 
@@ -513,8 +513,9 @@ def bench_design(args):
 # ---- rocprofv3 summaries (the files under profiles/) ------------------------
 
 KERNEL_SOURCES = ["paper_2012_13618_amd/csrc/" + f for f in (
-    "balance.hpp", "batch.hpp", "coarsen.hpp", "common.hpp", "engine.hip", "engine.hpp", "kway.hpp",
-    "level.hpp", "refine.hpp", "scan.hpp", "sched.hpp", "server.hpp", "transpose.hpp", "uncoarsen.hpp")]
+    "balance.hpp", "batch.hpp", "coarsen.hpp", "common.hpp", "engine.hip", "engine.hpp", "gain_lds.hpp",
+    "kway.hpp", "level.hpp", "match_lds.hpp", "refine.hpp", "scan.hpp", "sched.hpp", "server.hpp", "transpose.hpp",
+    "uncoarsen.hpp", "window.hpp")]
 
 
 def _read_csv(path):

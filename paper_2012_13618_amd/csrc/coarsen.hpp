@@ -2,7 +2,8 @@
 //
 //  match     Algorithm 1: every node takes the 64-bit minimum of
 //            (priority << 32 | hash(local id + 1)) over its hyperedges (a
-//            per-node reduction over the node-major incidence); the hash is a
+//            per-node reduction over the node-major incidence, or on coarse
+//            levels minima kept in LDS, match_lds.hpp); the hash is a
 //            bijection, so the winning hyperedge is decoded from the key.
 //  group     Algorithm 2, first loop: |S(e)| and the weight of S(e) by
 //            integer atomics; sets of two or more are merged.
@@ -14,8 +15,8 @@
 //  hedges    Algorithm 2, third loop: sorted distinct parents per hyperedge
 //            (registers / wave LDS / workgroup LDS / global by degree),
 //            kept when at least two.
-//  dedup     identical pin sets merged: fingerprint hash table with atomicMin
-//            of the source id, then an exact pin-by-pin check; weights added
+//  dedup     identical pin sets merged: a hash table of fingerprint bits over
+//            the smallest source id, then an exact pin-by-pin check; weights added
 //            into the surviving (smallest) source; compaction by scan.
 #pragma once
 #include "level.hpp"

@@ -140,29 +140,6 @@ template <typename K> __device__ __forceinline__ void block_rank_sort(const K *i
     __syncthreads();
 }
 
-// Same, but each wavefront sorts its own n-key slice (n a power of two); the
-// loop shape is identical for every wave so a workgroup barrier can be used.
-template <typename K> __device__ void wave_bitonic_sort(K *a, int n)
-{
-    int lane = threadIdx.x & 63;
-    for (int k = 2; k <= n; k <<= 1) {
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int i = lane; i < n; i += 64) {
-                int p = i ^ j;
-                if (p > i) {
-                    K x = a[i], y = a[p];
-                    bool up = (i & k) == 0;
-                    if ((x > y) == up) {
-                        a[i] = y;
-                        a[p] = x;
-                    }
-                }
-            }
-            __syncthreads();
-        }
-    }
-}
-
 __host__ __device__ inline int next_pow2(int x)
 {
     int p = 1;

@@ -1,7 +1,7 @@
-// Node-major incidence of a level: for every node, the ascending list of its
-// hyperedges (the bipartite graph of Section 1.1 read from the node side).
+// Node-major incidence of a level: for every node, the list of its hyperedges
+// (the bipartite graph of Section 1.1 read from the node side).
 //
-// Built by a stable LSD radix sort of (node id, hyperedge id) pairs taken in
+// Small levels: one workgroup (k_incidence_one).  Else built by a stable LSD radix sort of (node id, hyperedge id) pairs taken in
 // pin order, 8-bit digits: per-tile digit histograms, one prefix scan of the
 // (digit, tile) counts, and a stable scatter whose in-tile ranks come from
 // wavefront ballots and which writes each tile out in digit order.  The first

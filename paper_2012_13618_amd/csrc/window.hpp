@@ -26,8 +26,8 @@
 // What bounds a round is the latency of its four dependent launches (test and
 // marking, gain update, and these two); the selection that this replaces kept
 // ceil(n / 16384) workgroups at 31 us a round (chunk lists sorted and merged)
-// on segments of 133 K nodes, these two launches take 7 and 12 us (a round of
-// such a segment 45 -> 31 us).
+// on segments of 133 K nodes, these two launches take 5.5 and 9.3 us (a round of
+// such a segment 45 -> 31 us with tiles of 2048 nodes, 28 with tiles of 1024).
 #pragma once
 #include "uncoarsen.hpp"
 
@@ -35,7 +35,7 @@ namespace bp {
 
 constexpr int kWinBins = 1024;
 constexpr int kWinAbove = 0, kWinBelow = kWinBins - 1;
-constexpr int kWinItems = 8;
+constexpr int kWinItems = 4;  // (nodes a thread: 8, 4 and 2 gave 4 M column-nets k=8 92.5, 86.7 and 87.2 ms)
 constexpr int32_t kWinTile = kBlock * kWinItems;  // nodes a workgroup takes at a time
 constexpr int32_t kWinChunks = 512;               // chunks of a segment at most (same-bin atomics: 11 ns each)
 constexpr int64_t kWinTotal = 2048;               // chunks of a level, about

@@ -36,7 +36,7 @@ def check(bp, h, side, m0, m1, iters=0):
     assert np.array_equal(got.cpu().numpy(), ref) and gs == stuck
 
 
-@pytest.mark.parametrize("n", [1, 2, 63, 255, 2047, 2048, 2049, 4097, 50000])
+@pytest.mark.parametrize("n", [1, 2, 63, 255, 1023, 1024, 1025, 2047, 2048, 2049, 4097, 50000])
 @pytest.mark.parametrize("max_w", [1, 5, 400, 200000])
 def test_sizes_and_spans(bp, n, max_w):
     rng = np.random.default_rng(n + max_w)

@@ -515,6 +515,7 @@ __global__ __launch_bounds__(kBlock) void k_gain_nodes(int32_t N, int64_t ns, in
                 amax[i] = INT32_MIN;
                 amin[i] = INT32_MAX;
             }
+        __syncthreads();  // (not staged, no other barrier stands before the atomics on these)
         const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
         for (int64_t base = lo; base < hi; base += kBlock) {
             const int64_t v = base + threadIdx.x;

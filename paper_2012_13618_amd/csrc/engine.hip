@@ -1263,10 +1263,10 @@ static CutOut *launch_cut(Ctx &cx, const Input &in, int64_t P, int32_t k, const 
     const ValidateOut *ok = check ? &out->vo : nullptr;
     const double b = 8.0 * in.E + (bytes ? 5.0 : 8.0) * P;
     if (bytes)
-        launch(lc, "cut", b, k_cut<uint8_t>, cut_blocks(in.E), kCutThreads, 0, in.E, in.off, in.pins, in.hw,
+        launch(lc, "cut", b, k_cut<uint8_t>, cut_blocks(in.E, k), kCutThreads, 0, in.E, in.off, in.pins, in.hw,
                (const uint8_t *)bytes, mask64, k, (const unsigned long long *)pw, &out->cut, ok);
     else
-        launch(lc, "cut", b, k_cut<int32_t>, cut_blocks(in.E), kCutThreads, 0, in.E, in.off, in.pins, in.hw, d_part,
+        launch(lc, "cut", b, k_cut<int32_t>, cut_blocks(in.E, k), kCutThreads, 0, in.E, in.off, in.pins, in.hw, d_part,
                mask64, k, (const unsigned long long *)pw, &out->cut, ok);
     BP_HIP(hipMemcpyAsync(cx.info_h, out, sizeof(CutOut), hipMemcpyDeviceToHost, lc.stream));
     return (CutOut *)cx.info_h;

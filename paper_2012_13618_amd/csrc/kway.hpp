@@ -448,9 +448,11 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(int32_t E, const int32_t *o
     __shared__ int64_t lds64[16];
     if (ok && (ok->bad_offsets || ok->bad_pins)) return;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    if (blockIdx.x == 0) {
+    {
         unsigned long long m = 0;
-        for (int32_t i = tid; i < k; i += kCutThreads) m = pw[i] > m ? pw[i] : m;
+#pragma unroll 4
+        for (int64_t i = (int64_t)blockIdx.x * kCutThreads + tid; i < k; i += (int64_t)gridDim.x * kCutThreads)
+            m = pw[i] > m ? pw[i] : m;
         m = wave_max(m);
         if (lane == 0 && m) atomicMax(&acc[1], m);
     }
@@ -502,10 +504,11 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(int32_t E, const int32_t *o
     if (tid == 0 && contrib) atomicAdd(&acc[0], (unsigned long long)contrib);
 }
 
-// Workgroups of k_cut: as many as give each the same number of tiles.
-inline int64_t cut_blocks(int64_t E)
+// Workgroups of k_cut: as many as give each the same number of tiles, of the
+// hyperedges or (very many parts) of the part weights.
+inline int64_t cut_blocks(int64_t E, int32_t k)
 {
-    const int64_t tiles = std::max<int64_t>(ceil_div(E, kCutThreads), 1);
+    const int64_t tiles = std::max<int64_t>(ceil_div(std::max<int64_t>(E, k), kCutThreads), 1);
     return ceil_div(tiles, ceil_div(tiles, kCutMaxBlocks));
 }
 

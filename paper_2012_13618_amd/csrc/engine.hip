@@ -1226,11 +1226,12 @@ uint64_t eps_factor(int32_t k, double eps)
 }
 
 // Cut and part weights, queued: out (zeroed here) gets the validation's result
-// space, the cut and the heaviest part.  check: validate first; the cut is not
-// taken through pins that are not valid.
+// space, the cut, the heaviest part and the counts of listed hyperedges.  check:
+// validate first; the cut is not taken through pins that are not valid.
 struct CutOut {
     ValidateOut vo;
     unsigned long long cut, maxw;
+    int32_t large[2];
 };
 
 // From here the parts are gathered as bytes, the ints no longer staying in the
@@ -1256,18 +1257,23 @@ static CutOut *launch_cut(Ctx &cx, const Input &in, int64_t P, int32_t k, const 
     unsigned long long *pw = (unsigned long long *)(buf + words);
     fill(lc, buf, words + k, (uint64_t)0);
     if (check) launch_validate(cx, in, &out->vo);
-    const int mask64 = k <= 64 ? 1 : 0;
-    uint8_t *bytes = mask64 && in.N >= kCutBytesMin ? ar.get<uint8_t>(in.N) : nullptr;
+    uint8_t *bytes = k <= 64 && in.N >= kCutBytesMin ? ar.get<uint8_t>(in.N) : nullptr;
     launch(lc, "part_weights", 8.0 * in.N, k_part_weights, std::max<int64_t>(1, reduce_grid(in.N)), kBlock, 0, in.N,
            k, d_part, in.nw, bytes, pw);
     const ValidateOut *ok = check ? &out->vo : nullptr;
     const double b = 8.0 * in.E + (bytes ? 5.0 : 8.0) * P;
+    const int64_t blocks = cut_blocks(in.E, k);
+    const int lg = cut_run_bits(in.E, blocks);
+    int32_t *list = k > 64 ? ar.get<int32_t>(in.E) : nullptr;
     if (bytes)
-        launch(lc, "cut", b, k_cut<uint8_t>, cut_blocks(in.E, k), kCutThreads, 0, in.E, in.off, in.pins, in.hw,
-               (const uint8_t *)bytes, mask64, k, (const unsigned long long *)pw, &out->cut, ok);
+        launch(lc, "cut", b, k_cut<uint8_t>, blocks, kCutThreads, 0, in.E, lg, in.off, in.pins, in.hw,
+               (const uint8_t *)bytes, k, (const unsigned long long *)pw, &out->cut, list, out->large, ok);
     else
-        launch(lc, "cut", b, k_cut<int32_t>, cut_blocks(in.E, k), kCutThreads, 0, in.E, in.off, in.pins, in.hw, d_part,
-               mask64, k, (const unsigned long long *)pw, &out->cut, ok);
+        launch(lc, "cut", b, k_cut<int32_t>, blocks, kCutThreads, 0, in.E, lg, in.off, in.pins, in.hw, d_part, k,
+               (const unsigned long long *)pw, &out->cut, list, out->large, ok);
+    if (list)
+        launch(lc, "cut", 0.0, k_cut_large, std::min<int64_t>(in.E, kCutLargeBlocks), kBlock, 0, in.E, in.off, in.pins,
+               in.hw, d_part, (const int32_t *)list, (const int32_t *)out->large, &out->cut);
     BP_HIP(hipMemcpyAsync(cx.info_h, out, sizeof(CutOut), hipMemcpyDeviceToHost, lc.stream));
     return (CutOut *)cx.info_h;
 }

@@ -421,7 +421,7 @@ template <int S> inline int64_t cut_grid(int64_t count)
 // k part weights pw, to acc[1].  A workgroup takes tiles of kCutThreads
 // hyperedges: those of up to kHedgeThreadMax pins a thread each, with eight
 // gathers in flight; larger ones are queued and taken by wavefronts, and from
-// kCutHuge pins by the whole workgroup.  One barrier a tile: queue and counter
+// kCutHuge pins by the whole workgroup.  One barrier a tile: queue and counters
 // of a tile are not those of the next.
 //
 // The gathers of the pins' parts bound it, so they are bytes where the parts of
@@ -429,25 +429,39 @@ template <int S> inline int64_t cut_grid(int64_t count)
 // three launches by lists 82 us, and the lists' 12 and a readback; now 58 by
 // ints and 47 by bytes.  115 M pins over 10 M nodes: 2.73 ms, now 1.34.  Four
 // gathers in flight: 43 us and 1.45 ms.
+//
+// Large hyperedges that stand together would be one workgroup's work, so a tile
+// is made of runs of 2^lg hyperedges, one run of each 2^lg * gridDim.x (the
+// column-net of 617 K hyperedges sorted by size, k=16: tiles of consecutive ones
+// 636 us a call, now 229; unsorted 87 both ways).
+//
+// Above 64 parts a large hyperedge's work is its degree times the pins looked at
+// for each, which no fixed share evens out: there the larger ones go to a list
+// (those of up to kMidMax pins from its front, the others from its back; large
+// counts both) that k_cut_large takes (unsorted, k=128: 11.5 ms a call with the
+// tiles' own wavefronts, now 2.3; 1 M nodes of small hyperedges 171 and 183 us,
+// 291 by three launches and a readback).
+//
 // ok: nothing is read through the pins if it says that they are not valid.
 constexpr int kCutThreads = 512;
 constexpr int kCutMaxBlocks = 1024;  // (512 threads: two waves' worth of them fill the card)
 constexpr int32_t kCutHuge = 4096;
-constexpr int kCutHugeQueue = 64;
 
 template <typename PART>
-__global__ __launch_bounds__(kCutThreads) void k_cut(int32_t E, const int32_t *off, const int32_t *pins,
-                                                     const int32_t *hw, const PART *part, int mask64, int32_t k,
+__global__ __launch_bounds__(kCutThreads) void k_cut(int32_t E, int lg, const int32_t *off, const int32_t *pins,
+                                                     const int32_t *hw, const PART *part, int32_t k,
                                                      const unsigned long long *pw, unsigned long long *acc,
-                                                     const ValidateOut *ok)
+                                                     int32_t *list, int32_t *large, const ValidateOut *ok)
 {
-    __shared__ int32_t queue[2][kCutThreads], huge[2][kCutHugeQueue];
-    __shared__ int32_t nq[3], nh[3];
+    __shared__ int32_t queue[2][kCutThreads];  // wavefronts' from the front, the workgroup's from the back
+    __shared__ int32_t nq[3], nh[3], base[2];
     __shared__ unsigned long long orl[16];
     __shared__ int32_t lds[16];
     __shared__ int64_t lds64[16];
     if (ok && (ok->bad_offsets || ok->bad_pins)) return;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const bool mask64 = list == nullptr;
+    const int32_t huge = mask64 ? kCutHuge : kMidMax + 1;
     {
         unsigned long long m = 0;
 #pragma unroll 4
@@ -463,39 +477,47 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(int32_t E, const int32_t *o
     __syncthreads();
     int64_t contrib = 0;
     int t = 0, t3 = 0;
-    for (int64_t e0 = (int64_t)blockIdx.x * kCutThreads; e0 < E; e0 += (int64_t)gridDim.x * kCutThreads) {
-        const int32_t e = (int32_t)(e0 + tid);
+    const int64_t runs = kCutThreads >> lg;  // of a tile
+    for (int64_t r0 = 0; ((r0 * gridDim.x + blockIdx.x) << lg) < E; r0 += runs) {
+        const int64_t e = (((r0 + (tid >> lg)) * gridDim.x + blockIdx.x) << lg) + (tid & ((1 << lg) - 1));
         if (e < E) {
             const int32_t b = off[e], d = off[e + 1] - b;
-            int32_t h = kCutHugeQueue;
-            if (d >= kCutHuge) {
-                h = atomicAdd(&nh[t3], 1);
-                if (h < kCutHugeQueue) huge[t][h] = e;
-            }
-            if (d <= kHedgeThreadMax) {
-                if (d >= 2) {
-                    const int32_t lam = cut_lambda<1>(b, d, 0, pins, part, mask64, orl, lds);
-                    if (lam > 1) contrib += (int64_t)(hw ? hw[e] : 1) * (lam - 1);
-                }
-            } else if (h >= kCutHugeQueue) {
-                queue[t][atomicAdd(&nq[t3], 1)] = e;
+            if (d >= huge) {
+                queue[t][kCutThreads - 1 - atomicAdd(&nh[t3], 1)] = (int32_t)e;
+            } else if (d > kHedgeThreadMax) {
+                queue[t][atomicAdd(&nq[t3], 1)] = (int32_t)e;
+            } else if (d >= 2) {
+                const int32_t lam = cut_lambda<1>(b, d, 0, pins, part, mask64, orl, lds);
+                if (lam > 1) contrib += (int64_t)(hw ? hw[e] : 1) * (lam - 1);
             }
         }
         __syncthreads();
-        const int32_t n = nq[t3], m = min(nh[t3], kCutHugeQueue), free3 = t3 == 0 ? 2 : t3 - 1;
+        const int32_t n = nq[t3], m = nh[t3], free3 = t3 == 0 ? 2 : t3 - 1;
         if (tid == 0) {  // (the counters of the tile after the next, last read before this barrier)
             nq[free3] = 0;
             nh[free3] = 0;
         }
-        for (int32_t q = wv; q < n; q += kCutThreads / 64) {
-            const int32_t x = queue[t][q], b = off[x];
-            const int32_t lam = cut_lambda<64>(b, off[x + 1] - b, lane, pins, part, mask64, orl, lds);
-            if (lane == 0 && lam > 1) contrib += (int64_t)(hw ? hw[x] : 1) * (lam - 1);
-        }
-        for (int32_t q = 0; q < m; q++) {
-            const int32_t x = huge[t][q], b = off[x];
-            const int32_t lam = cut_lambda<kCutThreads>(b, off[x + 1] - b, tid, pins, part, mask64, orl, lds);
-            if (tid == 0 && lam > 1) contrib += (int64_t)(hw ? hw[x] : 1) * (lam - 1);
+        if (!mask64) {
+            if (n + m > 0) {
+                if (tid == 0) {
+                    base[0] = n ? atomicAdd(&large[0], n) : 0;
+                    base[1] = m ? atomicAdd(&large[1], m) : 0;
+                }
+                __syncthreads();
+                if (tid < n) list[base[0] + tid] = queue[t][tid];
+                if (tid < m) list[E - 1 - base[1] - tid] = queue[t][kCutThreads - 1 - tid];
+            }
+        } else {
+            for (int32_t q = wv; q < n; q += kCutThreads / 64) {
+                const int32_t x = queue[t][q], b = off[x];
+                const int32_t lam = cut_lambda<64>(b, off[x + 1] - b, lane, pins, part, true, orl, lds);
+                if (lane == 0 && lam > 1) contrib += (int64_t)(hw ? hw[x] : 1) * (lam - 1);
+            }
+            for (int32_t q = 0; q < m; q++) {
+                const int32_t x = queue[t][kCutThreads - 1 - q], b = off[x];
+                const int32_t lam = cut_lambda<kCutThreads>(b, off[x + 1] - b, tid, pins, part, true, orl, lds);
+                if (tid == 0 && lam > 1) contrib += (int64_t)(hw ? hw[x] : 1) * (lam - 1);
+            }
         }
         t ^= 1;
         t3 = t3 == 2 ? 0 : t3 + 1;
@@ -504,12 +526,52 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(int32_t E, const int32_t *o
     if (tid == 0 && contrib) atomicAdd(&acc[0], (unsigned long long)contrib);
 }
 
-// Workgroups of k_cut: as many as give each the same number of tiles, of the
-// hyperedges or (very many parts) of the part weights.
+// The listed hyperedges of a cut of more than 64 parts: a workgroup each from
+// the back of the list, then a wavefront each from its front.
+constexpr int64_t kCutLargeBlocks = 2048;
+__global__ __launch_bounds__(kBlock) void k_cut_large(int32_t E, const int32_t *off, const int32_t *pins,
+                                                      const int32_t *hw, const int32_t *part, const int32_t *list,
+                                                      const int32_t *large, unsigned long long *acc)
+{
+    __shared__ int32_t lds[16];
+    __shared__ int64_t lds64[16];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int32_t n = large[0], m = large[1];
+    int64_t contrib = 0;
+    for (int64_t q = blockIdx.x; q < m; q += gridDim.x) {
+        const int32_t x = list[E - 1 - q], b = off[x];
+        const int32_t lam = cut_lambda<kBlock>(b, off[x + 1] - b, tid, pins, part, false, nullptr, lds);
+        if (tid == 0 && lam > 1) contrib += (int64_t)(hw ? hw[x] : 1) * (lam - 1);
+    }
+    for (int64_t q = (int64_t)blockIdx.x * (kBlock / 64) + (tid >> 6); q < n; q += (int64_t)gridDim.x * (kBlock / 64)) {
+        const int32_t x = list[q], b = off[x];
+        const int32_t lam = cut_lambda<64>(b, off[x + 1] - b, lane, pins, part, false, nullptr, lds);
+        if (lane == 0 && lam > 1) contrib += (int64_t)(hw ? hw[x] : 1) * (lam - 1);
+    }
+    contrib = block_sum(contrib, lds64);
+    if (tid == 0 && contrib) atomicAdd(&acc[0], (unsigned long long)contrib);
+}
+
+// Workgroups of k_cut: as many as give each the same number of whole tiles (of
+// the hyperedges or, with very many parts, of the part weights); for few
+// hyperedges up to kCutSpread of eight each, as many as there are wavefronts,
+// should they be large (a call with 512 of 2000 pins: by one workgroup 574 us, now
+// 45; by a list and a workgroup each 139).
+constexpr int64_t kCutSpread = 256;
 inline int64_t cut_blocks(int64_t E, int32_t k)
 {
     const int64_t tiles = std::max<int64_t>(ceil_div(std::max<int64_t>(E, k), kCutThreads), 1);
-    return ceil_div(tiles, ceil_div(tiles, kCutMaxBlocks));
+    if (tiles >= kCutSpread) return ceil_div(tiles, ceil_div(tiles, kCutMaxBlocks));
+    return std::max(tiles, std::min(ceil_div(E, 8), kCutSpread));
+}
+
+// log2 of k_cut's runs: a wavefront's hyperedges, shorter where that would leave
+// a workgroup without a run.
+inline int cut_run_bits(int64_t E, int64_t blocks)
+{
+    int lg = 0;
+    while (lg < 6 && (E >> (lg + 1)) >= blocks) lg++;
+    return lg;
 }
 
 // Part weights: registers for k <= 8, an LDS histogram for k <= 4096, else

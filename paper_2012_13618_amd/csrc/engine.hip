@@ -2205,7 +2205,7 @@ bp_status bp_autotune_batch_device(int32_t n, const bp_hypergraph *graphs, const
     run(base, ref_cuts, ref_parts);  // also warms the device memory pool
     std::vector<Schedule> cand;
     for (int32_t inc : {1 << 16, 1 << 18, 1 << 20, INT32_MAX})
-        for (int32_t seg : {0, 4096, 16384, 32768})
+        for (int32_t seg : {0, 4096, kSegSelectMax})
             for (int32_t chunk : {16, 32})
                 cand.push_back(
                     Schedule{inc, seg, chunk, base.fused_pick_lists, base.fuse_max_pins, base.chunk_select_max_nodes,

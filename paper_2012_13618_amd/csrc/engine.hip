@@ -953,7 +953,7 @@ void bisect_all(Ctx &cx, Level &L0, Segs &sg, int32_t active0)
             const Level &x = lv[j];
             fl.lv[j - bottom] = FuseLevel{x.off, x.pins, x.hw, x.noff, x.inc, x.nw, x.nbase, x.hbase, x.parent};
             bytes += 4.0 * x.P + 12.0 * x.N;
-            cx.pins_refined += x.P * (int64_t)std::max(cx.prm.refine_iters, 1);
+            cx.pins_refined += (int64_t)x.P * cx.prm.refine_iters;  // (as on the levels above)
         }
         fl.S = L0.S;
         fl.top = top;

@@ -37,6 +37,22 @@ static void set_schedule(const Schedule &s)
     g_sched = s;
 }
 
+// Whether a level's selections run in one workgroup per segment; that kernel computes its lists' sizes and gain
+// extremes itself, so the gain passes need not.
+static bool seg_path(const Ctx &cx, const Level &L)
+{
+    return L.maxseg_nodes <= std::min(cx.sched.seg_select_max_nodes, kSegSelectMax);
+}
+
+// Whether a level's balance selections are windowed (window.hpp): segments too
+// large for one workgroup, up to the schedule's limit (none at its largest
+// value).
+static bool win_path(const Ctx &cx, const Level &L)
+{
+    const int32_t lim = cx.sched.chunk_select_max_nodes;
+    return !seg_path(cx, L) && lim > 0 && (lim >= kChunkSelectCap || L.maxseg_nodes <= lim);
+}
+
 // ---- one coarsening step ------------------------------------------------------
 
 // The coarse level's hyperedge lists by degree (blocks [0, ncls)) and the copy
@@ -60,13 +76,18 @@ void coarsen_level(Ctx &cx, Level &f, Segs &sg, uint8_t *&sact, uint8_t *&sact_n
     check_lists(f);
     cx.pins_coarsened += P;
     CoarsenBufs b;
-    b.key = ar.get<uint64_t>(N);
+    // (the first level's with room for what balance rounds and gains keep there)
+    f.spent_keys_n = std::max<int64_t>(N, l == 0 && win_path(cx, f) ? win_chunks(f) * kWinBins : 0);
+    b.key = ar.get<uint64_t>(f.spent_keys_n);
+    f.spent_keys = (unsigned long long *)b.key;
     b.match = ar.get<int32_t>(N);
     b.grp = ar.get<int32_t>(N);
     b.cid = ar.get<int32_t>(N);
     b.cg = ar.get<uint64_t>(E);
     b.lead = ar.get<int32_t>(E);
-    b.qpins = ar.get<int32_t>(P);
+    f.spent_pins_n = std::max<int64_t>(P, l == 0 && gl_ok(f) ? gl_parts(f) : 0);
+    b.qpins = ar.get<int32_t>(f.spent_pins_n);
+    f.spent_pins = b.qpins;
     b.qlen = ar.get<int32_t>(E);
     b.fp = ar.get<uint64_t>(E);
     b.hslot = ar.get<int32_t>(E);
@@ -433,13 +454,12 @@ static void build_gain_slabs(Ctx &cx, Level *lv, int32_t n)
         Level &L = lv[j];
         if (!gl_ok(L)) continue;
         GainSlabs &gs = L.gs;
-        gs.pps = (int32_t)ceil_div(L.P, gl_slabs(L));
+        gs.pps = gl_pps(L);
         gs.bound = L.S + (int32_t)ceil_div(L.P, gs.pps);
         gs.rec = ar.get<int4>(gs.bound);
         gs.slab0 = ar.get<int32_t>((int64_t)L.S + 1);
         gs.pbase = ar.get<int64_t>(L.S);
-        // sum over the segments of (1 + pins / pps) times their nodes
-        parts = std::max(parts, (int64_t)L.N + ceil_div(L.P, gs.pps) * L.maxseg_nodes);
+        parts = std::max(parts, gl_parts(L));
         on.push_back(&L);
         ta.off[q] = L.off;
         ta.nbase[q] = L.nbase;
@@ -450,7 +470,7 @@ static void build_gain_slabs(Ctx &cx, Level *lv, int32_t n)
     }
     flush();
     if (on.empty()) return;
-    int32_t *part = ar.get<int32_t>(parts);
+    int32_t *part = parts <= lv[0].spent_pins_n ? lv[0].spent_pins : ar.get<int32_t>(parts);
     for (Level *L : on) L->gs.part = part;
 }
 
@@ -510,22 +530,6 @@ void run_select(Ctx &cx, Level &L, Segs &sg, const int32_t *gain, const int32_t 
 
 static void flip(Ctx &cx, Level &L, Segs &sg, const int32_t *gain, const int32_t *go);
 
-// Whether a level's selections run in one workgroup per segment; that kernel computes its lists' sizes and gain
-// extremes itself, so the gain passes need not.
-static bool seg_path(const Ctx &cx, const Level &L)
-{
-    return L.maxseg_nodes <= std::min(cx.sched.seg_select_max_nodes, kSegSelectMax);
-}
-
-// Whether a level's balance selections are windowed (window.hpp): segments too
-// large for one workgroup, up to the schedule's limit (none at its largest
-// value).
-static bool win_path(const Ctx &cx, const Level &L)
-{
-    const int32_t lim = cx.sched.chunk_select_max_nodes;
-    return !seg_path(cx, L) && lim > 0 && (lim >= kChunkSelectCap || L.maxseg_nodes <= lim);
-}
-
 // Buffers of the windowed selections of n levels (none when no level has one).
 static void alloc_win(Ctx &cx, Segs &sg, const Level *lv, int32_t n)
 {
@@ -533,7 +537,7 @@ static void alloc_win(Ctx &cx, Segs &sg, const Level *lv, int32_t n)
     int64_t chunks = 0;
     for (int32_t j = 0; j < n; j++)
         if (win_path(cx, lv[j]))
-            chunks = std::max(chunks, ceil_div(lv[j].N, win_chunk_nodes(lv[j].maxseg_nodes, lv[j].N)) + lv[j].S);
+            chunks = std::max(chunks, win_chunks(lv[j]));
     if (chunks == 0) return;
     Arena &ar = *cx.ar;
     WinState &w = sg.win;
@@ -541,7 +545,8 @@ static void alloc_win(Ctx &cx, Segs &sg, const Level *lv, int32_t n)
     w.top = ar.get<int32_t>(4 * S);
     w.shift = ar.get<int32_t>(4 * S);
     w.tot = ar.get<unsigned long long>(3 * S * kWinBins);
-    w.rows = ar.get<unsigned long long>(chunks * kWinBins);
+    w.rows = chunks * kWinBins <= lv[0].spent_keys_n ? lv[0].spent_keys
+                                                     : ar.get<unsigned long long>(chunks * kWinBins);
     w.tab = ar.get<int4>(chunks);
     w.tab_n = chunks;
     w.pend = ar.get<int32_t>(3 * S);
@@ -830,7 +835,7 @@ static int64_t refine_level(Ctx &cx, Level &L, Segs &sg, int32_t j, int32_t *gai
     if (win) {
         const int32_t cn = win_chunk_nodes(L.maxseg_nodes, L.N);
         WinState &w = sg.win;
-        nct = ceil_div(L.N, cn) + L.S;
+        nct = win_chunks(L);
         if (!w.rows || nct > w.tab_n) throw Error(BP_ERR_DEVICE, "windowed selection buffers missing");
         wa = WinArgs{L.S, L.N, w.tab, gain, L.nw, sg.m, sg.mode, L.side, sg.need, sg.room,
                      (unsigned long long *)sg.w, w, ml, 0, 0, nullptr};

@@ -313,4 +313,9 @@ inline int32_t gl_slabs(const Level &L)
     return (int32_t)std::max<int64_t>(1, std::min(x, cap));
 }
 
+// pins a slab, and partial sums of a level: over the segments, (1 + pins / pps)
+// times their nodes
+inline int32_t gl_pps(const Level &L) { return (int32_t)ceil_div(L.P, gl_slabs(L)); }
+inline int64_t gl_parts(const Level &L) { return (int64_t)L.N + ceil_div(L.P, gl_pps(L)) * L.maxseg_nodes; }
+
 }  // namespace bp

@@ -62,6 +62,11 @@ struct Level {
     int32_t *tfirst = nullptr;   // hyperedge holding the first pin of each radix tile, once known
     int2 *tnext = nullptr;       // first hyperedge that starts in each quarter tile or after it, and its first pin
     uint32_t *counts0 = nullptr; // the radix tiles' histograms of the first digit, once taken
+    // scratch of its coarsening step, free once that is done: the balance rounds
+    // and gains of the bisection work in the first level's
+    unsigned long long *spent_keys = nullptr;
+    int32_t *spent_pins = nullptr;
+    int64_t spent_keys_n = 0, spent_pins_n = 0;
 };
 
 // Sizes and counters read back once per level.

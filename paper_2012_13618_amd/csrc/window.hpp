@@ -49,6 +49,12 @@ inline int32_t win_chunk_nodes(int64_t maxseg, int64_t N)
     return (int32_t)(std::max<int64_t>(t, 1) * kWinTile);
 }
 
+// chunks of a level at most
+inline int64_t win_chunks(const Level &L)
+{
+    return ceil_div(L.N, win_chunk_nodes(L.maxseg_nodes, L.N)) + L.S;
+}
+
 struct WinArgs {
     int32_t S, N;  // segments, nodes of the level
     const int4 *tab;

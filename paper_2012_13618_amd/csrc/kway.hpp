@@ -462,7 +462,7 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(int32_t E, int lg, const in
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const bool mask64 = list == nullptr;
     const int32_t huge = mask64 ? kCutHuge : kMidMax + 1;
-    {
+    if ((int64_t)blockIdx.x * kCutThreads < k) {
         unsigned long long m = 0;
 #pragma unroll 4
         for (int64_t i = (int64_t)blockIdx.x * kCutThreads + tid; i < k; i += (int64_t)gridDim.x * kCutThreads)

@@ -421,13 +421,12 @@ void run_gains(Ctx &cx, Level &L, Segs &sg, int32_t *gain, bool stats, const int
     if (nzb)
         launch(lc, "gain_nodes", (cb + 0.125) * L.E, k_nz_bits, ceil_div(L.E, kBlock), kBlock, 0, L.E,
                (const void *)L.cc, L.cc_pk, (unsigned long long *)nzb, go);
-    int32_t nw = (int32_t)std::min<int64_t>(ceil_div(L.nmid_bound, kBlock / 64), kGnBlocks);
-    // with stats, at most kGnBlocks workgroups end in the lists' atomics
-    const bool staged = (int64_t)L.N >= kGnStagedMin;
-    const int64_t ns = stats ? std::min<int64_t>(ceil_div(L.N, kBlock), kGnBlocks) : ceil_div(L.N, kBlock);
+    const bool staged = gn_staged(L);
+    int32_t nw = (int32_t)std::min(ceil_div(L.nmid_bound, kBlock / 64), gn_wave_blocks(L));
+    const int64_t ns = stats ? std::min(ceil_div(L.N, kBlock), gn_blocks(L)) : ceil_div(L.N, kBlock);
     int64_t nv = ns + nw + L.nchunk_bound;
     double nb = 8.0 * L.N + 4.0 * L.P + cb * L.P + 1.0 * L.N + 4.0 * L.N;
-    launch(lc, "gain_nodes", nb, k_gain_nodes, nv, kBlock, 0, L.N, ns, staged ? 1 : 0, (const int32_t *)L.lnmid,
+    launch(lc, "gain_nodes", nb, staged ? &k_gain_nodes<true> : &k_gain_nodes<false>, nv, kBlock, 0, L.N, ns, (const int32_t *)L.lnmid,
            (const int32_t *)L.lnbig, (const int32_t *)L.ncount, (const int32_t *)L.noff,
            (const int32_t *)L.inc, (const int32_t *)L.nseg, (const uint8_t *)sg.gmask,
            (const uint8_t *)L.side, (const void *)L.cc, L.cc_pk, (const uint32_t *)nzb, gain,

@@ -435,13 +435,16 @@ __global__ __launch_bounds__(kBlock) void k_nz_bits(int32_t E, const void *cc, i
 }
 
 // A lane's share (lane, lane + stride, ...) of the contributions to a node on
-// side sd over its incidences b .. b + d, eight loads in flight at a time.
+// side sd over its incidences b .. b + d, eight loads in flight at a time (none
+// for the places past the degree: as loads of the last one they cost as much
+// as the others; and the sums apart from the loads, or each waits for its own).
 __device__ __forceinline__ int32_t gather_sum(int32_t b, int32_t d, int lane, int stride, const int32_t *inc,
                                               const void *cc, int pk, const uint32_t *nzb, int sd)
 {
     int32_t g = 0;
     for (int32_t i0 = lane; i0 < d; i0 += 8 * stride) {
         int32_t e[8];
+        int2 c[8];
         bool in[8];
 #pragma unroll
         for (int k = 0; k < 8; k++) {
@@ -453,32 +456,27 @@ __device__ __forceinline__ int32_t gather_sum(int32_t b, int32_t d, int lane, in
             for (int k = 0; k < 8; k++) in[k] = in[k] && ((nzb[e[k] >> 5] >> (e[k] & 31)) & 1);
         }
 #pragma unroll
-        for (int k = 0; k < 8; k++) {
-            if (!in[k]) continue;
-            const int2 c = cc_get(cc, pk, e[k]);
-            g += sd ? c.y : c.x;
-        }
+        for (int k = 0; k < 8; k++) c[k] = in[k] ? cc_get(cc, pk, e[k]) : make_int2(0, 0);
+#pragma unroll
+        for (int k = 0; k < 8; k++) g += sd ? c[k].y : c[k].x;
     }
     return g;
 }
 
-constexpr int64_t kGnStagedMin = 1 << 18;
-constexpr int64_t kGnBlocks = 2048;  // workgroups of the node pass that end in the lists' atomics (11 ns each)
 constexpr int32_t kGnThread = 64;    // node degree: staged and summed by a thread; above: a wavefront
 
 // Node pass.  Besides gain[v], per-list counts and gain extremes for the
 // selection that follows (block-aggregated when a block is in one segment).
 //
-// The first ns blocks take runs of nodes, 256 at a time: the incidences of
-// those of degree <= kGnThread are loaded in order, 16 a thread, their
-// contributions gathered and staged in LDS, and a thread a node sums its own.
-// On smaller levels (not staged) a thread gathers its node's contributions
-// itself, two memory round trips for every eight incidences of the wavefront's
-// largest node: fewer workgroups than the chip holds, so only their latency
-// counts (12 K nodes 8.4 us, staged 11.2; 1 M nodes 76 us, staged 68).  nzb (nullable): the
-// contributions that are not zero.  Bound by the gathers: 115 M incidences of
-// 10 M hyperedges 1.9 ms, now 0.92; 5.4 M of 1.2 M 76 us, now 68.
-__global__ __launch_bounds__(kBlock) void k_gain_nodes(int32_t N, int64_t ns, int staged, const int32_t *lnmid,
+// The first ns blocks take runs of nodes, 256 at a time.  A thread gathers its
+// node's contributions itself, two memory round trips for every eight
+// incidences of the wavefront's largest node.  STAGED: the incidences of those
+// of degree <= kGnThread are loaded in order, 16 a thread, their contributions
+// gathered and staged in LDS, and a thread a node sums its own.  nzb (nullable):
+// the contributions that are not zero.  Bound by the gathers: 115 M incidences
+// of 10 M hyperedges 1.9 ms, now 0.92 (staged).
+template <bool STAGED>
+__global__ __launch_bounds__(kBlock) void k_gain_nodes(int32_t N, int64_t ns, const int32_t *lnmid,
                                                        const int32_t *lnbig, const int32_t *ncount,
                                                        const int32_t *noff, const int32_t *inc,
                                                        const int32_t *nseg, const uint8_t *gmask,
@@ -497,7 +495,7 @@ __global__ __launch_bounds__(kBlock) void k_gain_nodes(int32_t N, int64_t ns, in
     if (go && *go == 0) return;
     bool stats = tot != nullptr;
     int32_t cm = ncount[0], ck = ncount[2];
-    const int32_t thread_max = staged ? kGnThread : kNodeSmallMax;
+    const int32_t thread_max = STAGED ? kGnThread : kNodeSmallMax;
     int64_t vb = blockIdx.x;
     if (vb < ns) {
         __shared__ int32_t val[kRsTile];  // where a node's incidences start, then the gathered contributions
@@ -531,9 +529,9 @@ __global__ __launch_bounds__(kBlock) void k_gain_nodes(int32_t N, int64_t ns, in
             }
             if (!on) d = 0;
             int32_t T = 0, st = 0, g = 0;
-            if (staged) st = block_excl_scan(d, lds, &T);
+            if (STAGED) st = block_excl_scan(d, lds, &T);
             else if (d > 0) g = gather_sum(b, d, 0, 1, inc, cc, pk, nzb, sd);
-            for (int32_t t0 = 0; t0 < T; t0 += kRsTile) {
+            for (int32_t t0 = 0; STAGED && t0 < T; t0 += kRsTile) {
                 // each staged position's incidence: st + (b - st)
                 if (threadIdx.x < 64) tl.bits[threadIdx.x] = 0;
                 if (threadIdx.x == 0) carry = 0;
@@ -686,6 +684,27 @@ __global__ __launch_bounds__(kBlock) void k_gain_nodes(int32_t N, int64_t ns, in
         }
     }
 }
+
+// Whether the node pass stages: where a level fills the card many times over
+// and has eight incidences a node.  By a thread each / staged, ids near / far
+// apart: 1 M nodes of 6 incidences 24, 33 / 27, 35 us, of 10 35, 53 / 33, 52;
+// 3 M of 6 61, 98 / 62, 99, of 10 103, 168 / 86, 169; 600 K of 10 27, 36 / 29, 46.
+inline bool gn_staged(const Level &L) { return L.N >= (1 << 20) && (int64_t)L.P >= 8 * (int64_t)L.N; }
+
+// Blocks of the node pass that end in the lists' atomics, at most: each costs
+// some 9 ns there, so fewer where they have little else to do.  At 512, 1024 and
+// 2048: 300 K nodes of no incidence 11, 13, 18 us, of 4 16, 17, 22; 600 K of none
+// 13, 16, 19, of 4 21, 22, 30; 1 M of none 16, 18, 27, of 4 30, 27, 37; 3 M of 4
+// 56, 41, 42.
+inline int64_t gn_blocks(const Level &L)
+{
+    if (gn_staged(L)) return 2048;
+    return L.N >= (3 << 18) && (int64_t)L.P >= L.N / 16 ? 1024 : 512;
+}
+
+// The same of its blocks of listed nodes, four at a time.  At 512, 1024 and 2048:
+// 17 K nodes of 40 incidences 19, 20, 24 us, 60 K 54, 39, 45, 150 K of 100 92, 66, 74.
+inline int64_t gn_wave_blocks(const Level &L) { return L.N >= (1 << 15) ? 1024 : 512; }
 
 // Per-list counts and gain extremes after a gain update (what the node pass
 // records otherwise); clears the move marks and the hyperedge list.  Chunked:

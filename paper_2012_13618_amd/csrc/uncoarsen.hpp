@@ -97,9 +97,13 @@ __global__ __launch_bounds__(kBlock) void k_side_bits(int32_t N, const uint8_t *
 // bits: the whole workgroup counts the rest of it.  n1out (nullable): the
 // counts, for incremental rounds.  Bound by the side gathers (sbits or side):
 // 115 M pins over 10 M nodes 2.3 ms, now 0.57; 5.4 M over 1 M 61 us, now 38.
-// Levels of few pins take quarter tiles (R = 4), as only a tile's latency
-// counts there (93 K pins: R = 16 7.6 us, R = 4 4.9).
-constexpr int64_t kGhSmall = 1 << 20;
+// Up to 2^22 pins quarter tiles (R = 4), as whole ones do not fill the card (pins
+// near / far apart, R = 16 and R = 4: 93 K pins 7.6 and 4.9 us, 1.5 M 13, 16 and
+// 11.4, 14.3; 5 M 18.2, 28.8 and 19.3, 28.1; 16 M 25.7, 42 and 28.8, 42.8).
+// The rest of a hyperedge longer than its tile is 16 pins a thread at a time,
+// with the next ones' ids loaded meanwhile: one of 500 K pins 474 us with 8 and
+// nothing ahead, now 94.
+constexpr int64_t kGhSmall = 1 << 22;
 template <int R>
 __global__ __launch_bounds__(kBlock) void k_gain_hedges(int32_t E, int32_t P, int64_t ntiles, const int32_t *off,
                                                         const int32_t *pins, const int32_t *hw,
@@ -172,14 +176,25 @@ __global__ __launch_bounds__(kBlock) void k_gain_hedges(int32_t E, int32_t P, in
     // the one that holds the next tile's first pin
     const int32_t el = ee - 1, b = off[el] - p0, d = past.y - p0 - b;
     if (!gmask[hseg[el]]) return;
-    int32_t n1 = 0;
-    for (int32_t i0 = kTile + (int32_t)threadIdx.x; i0 < b + d; i0 += 8 * kBlock) {
-        int32_t q[8];
+    constexpr int T = 16;
+    const int32_t end = b + d;
+    int32_t n1 = 0, q[T], nq[T];
+    auto load = [&](int32_t i0, int32_t (&id)[T]) {
 #pragma unroll
-        for (int k = 0; k < 8; k++) q[k] = pins[p0 + min(i0 + k * kBlock, b + d - 1)];
+        for (int k = 0; k < T; k++) id[k] = pins[p0 + min(i0 + (int32_t)threadIdx.x + k * kBlock, end - 1)];
+    };
+    load(kTile, q);
+    for (int32_t i0 = kTile; i0 < end; i0 += T * kBlock) {
+        const bool more = end - i0 > T * kBlock;
+        if (more) load(i0 + T * kBlock, nq);
 #pragma unroll
-        for (int k = 0; k < 8; k++)
-            if (i0 + k * kBlock < b + d) n1 += side[q[k]];
+        for (int k = 0; k < T; k++) q[k] = side[q[k]];
+#pragma unroll
+        for (int k = 0; k < T; k++)
+            if (i0 + (int32_t)threadIdx.x + k * kBlock < end) n1 += q[k];
+        if (more)
+#pragma unroll
+            for (int k = 0; k < T; k++) q[k] = nq[k];
     }
     n1 = block_sum(n1, lds) + count_bits(bits, b, kTile);
     if (threadIdx.x == 0) {

@@ -838,7 +838,7 @@ static int64_t refine_level(Ctx &cx, Level &L, Segs &sg, int32_t j, int32_t *gai
         if (!w.rows || nct > w.tab_n) throw Error(BP_ERR_DEVICE, "windowed selection buffers missing");
         wa = WinArgs{L.S, L.N, w.tab, gain, L.nw, sg.m, sg.mode, L.side, sg.need, sg.room,
                      (unsigned long long *)sg.w, w, ml, 0, 0, nullptr};
-        launch(lc, "balance", 0.0, k_win_table, 1, 1024, 0, L.S, cn, (const int32_t *)L.nbase, nct, w);
+        launch(lc, "balance", 0.0, k_win_table, 1, kWinTabSegs, 0, L.S, cn, (const int32_t *)L.nbase, nct, w);
     }
     int64_t lg = std::max<int64_t>(1, std::min<int64_t>(ceil_div((int64_t)L.P / kLogChunk + L.N, kBlock / 64), 1024));
     int64_t ugrid = std::max<int64_t>(1, std::min<int64_t>(ceil_div(nbits, kUpdWords), 2048));

@@ -78,25 +78,41 @@ __device__ __forceinline__ int win_bin(int32_t gain, int32_t top, int32_t shift)
 
 // The chunk table of a level - segment, first node, nodes, the segment's first
 // chunk; up to `bound` entries, the ones past the last chunk without nodes -
-// and its first window, the last one of the level before.
-__global__ __launch_bounds__(1024) void k_win_table(int32_t S, int32_t cn, const int32_t *nbase, int64_t bound,
-                                                    WinState win)
+// and its first window, the last one of the level before.  The entries are
+// shared out over the threads, kWinTabSegs segments at a time: written by a
+// thread a segment they took 20 us for one of 1 M nodes (2 now).
+constexpr int kWinTabSegs = 1024;
+__global__ __launch_bounds__(kWinTabSegs) void k_win_table(int32_t S, int32_t cn, const int32_t *nbase, int64_t bound,
+                                                           WinState win)
 {
-    __shared__ int32_t lds[16];
+    __shared__ int32_t lds[16], first[kWinTabSegs], node[kWinTabSegs];  // of each segment: its first chunk, its first node
+    const int tid = threadIdx.x;
     int32_t carry = 0;
-    for (int32_t base = 0; base < S; base += blockDim.x) {
-        int32_t s = base + (int32_t)threadIdx.x;
-        int32_t a = s < S ? nbase[s] : 0, n = s < S ? nbase[s + 1] - a : 0;
-        int32_t c = (n + cn - 1) / cn, tot;
-        int32_t at = block_excl_scan(c, lds, &tot) + carry;
-        for (int32_t i = 0; i < c; i++) win.tab[at + i] = make_int4(s, a + i * cn, min(n - i * cn, cn), at);
+    for (int32_t base = 0; base < S; base += kWinTabSegs) {
+        const int32_t s = base + tid, a = s < S ? nbase[s] : 0, n = s < S ? nbase[s + 1] - a : 0;
+        int32_t tot;
+        const int32_t at = block_excl_scan((n + cn - 1) / cn, lds, &tot) + carry;
+        first[tid] = at;
+        node[tid] = a;
         if (s < S) {
             win.top[s] = win.top[3 * S + s];
             win.shift[s] = win.shift[3 * S + s];
         }
+        __syncthreads();
+        for (int32_t i = carry + tid; i < carry + tot; i += kWinTabSegs) {
+            int lo = 0, hi = kWinTabSegs;  // the last segment that starts at chunk i or before (empty ones start where the next does)
+            while (hi - lo > 1) {
+                const int mid = (lo + hi) >> 1;
+                if (first[mid] <= i) lo = mid;
+                else hi = mid;
+            }
+            const int32_t b = node[lo] + (i - first[lo]) * cn;
+            win.tab[i] = make_int4(base + lo, b, min(nbase[base + lo + 1] - b, cn), first[lo]);
+        }
         carry += tot;
+        __syncthreads();
     }
-    for (int64_t i = carry + threadIdx.x; i < bound; i += blockDim.x) win.tab[i] = make_int4(0, 0, 0, 0);
+    for (int64_t i = carry + tid; i < bound; i += kWinTabSegs) win.tab[i] = make_int4(0, 0, 0, 0);
 }
 
 // A thread's nodes of a tile: gains, sides and weights, loaded together (past

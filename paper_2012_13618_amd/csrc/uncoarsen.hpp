@@ -700,11 +700,15 @@ __global__ __launch_bounds__(kBlock) void k_gain_nodes(int32_t N, int64_t ns, co
     }
 }
 
-// Whether the node pass stages: where a level fills the card many times over
-// and has eight incidences a node.  By a thread each / staged, ids near / far
-// apart: 1 M nodes of 6 incidences 24, 33 / 27, 35 us, of 10 35, 53 / 33, 52;
-// 3 M of 6 61, 98 / 62, 99, of 10 103, 168 / 86, 169; 600 K of 10 27, 36 / 29, 46.
-inline bool gn_staged(const Level &L) { return L.N >= (1 << 20) && (int64_t)L.P >= 8 * (int64_t)L.N; }
+// Whether the node pass stages: on levels of many pins, eight a node at least.  By
+// a thread each / staged, ids near / far apart: 1 M nodes of 6 incidences 24, 33 /
+// 27, 35 us, of 10 35, 53 / 33, 52; 3 M of 6 61, 98 / 62, 99, of 10 103, 168 / 86,
+// 169; 600 K of 10 27, 36 / 29, 46; coarse levels of 0.3 M nodes and 104 M pins
+// 794 / 623 and 1214 / 919 (degrees from a few to thousands).
+inline bool gn_staged(const Level &L)
+{
+    return L.N >= (1 << 18) && (int64_t)L.P >= std::max<int64_t>(8 * (int64_t)L.N, 1 << 23);
+}
 
 // Blocks of the node pass that end in the lists' atomics, at most: each costs
 // some 9 ns there, so fewer where they have little else to do.  At 512, 1024 and

@@ -381,8 +381,9 @@ __device__ __forceinline__ uint64_t gain_order_key(int32_t gain, uint32_t id)
 // by such atomics needs no more than this before a ticket (itself an atomic)
 // announces it; a release fence would write back the XCD's whole L2 as well,
 // which every workgroup of a large grid pays for in turn (node gain pass of a
-// 134 K-node level with 1600 chunks of big nodes: 121 us, now 53).  The side
-// that reads after the ticket still acquires.
+// 134 K-node level with 1600 chunks of big nodes: 121 us, now 53).  What is
+// stored plainly before a ticket needs the fence.  The side that reads after
+// the ticket still acquires.
 __device__ __forceinline__ void atomics_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // ---- wave64 / workgroup collectives -------------------------------------------

@@ -98,8 +98,12 @@ struct SelState {
 
 // Windowed balance selection (window.hpp); null where no level uses it.
 struct WinState {
-    int32_t *top = nullptr, *shift = nullptr;  // [2][S] the segments' windows, by round parity
-    unsigned long long *tot = nullptr;         // [2][S][kWinBins] segment histograms, by round parity
+    // [4][S] the segments' windows: round i's in row i % 3, in row 3 the last one,
+    // which the next level starts from
+    int32_t *top = nullptr, *shift = nullptr;
+    // [3][S][kWinBins] the segments' histograms, round i's in slot i % 3 (its moves
+    // clear the next round's)
+    unsigned long long *tot = nullptr;
     unsigned long long *rows = nullptr;        // [chunks][kWinBins] the chunks' histograms
     int4 *tab = nullptr;                       // chunk table, tab_n entries
     int64_t tab_n = 0;

@@ -65,7 +65,7 @@ constexpr int kLogChunk = 64;  // incidences of a moved node per logged chunk
 struct MoveLog {
     const int32_t *noff;
     int32_t *cnode, *cbeg;
-    int32_t *count;  // [0] logged chunks, [1] listed small hyperedges, [2] listed big ones
+    int32_t *count;  // [0] logged chunks
 };
 
 // Logs the moves of the first p keys' nodes (one workgroup).

@@ -4,9 +4,9 @@
 // on each side gains from its hyperedge (+w when alone on its side, -w when
 // the hyperedge is uncut), and a node pass summing that over the node's
 // hyperedges.  The hyperedge pass takes a tile of pins a workgroup.  The node
-// pass's first blocks take 256 nodes at a time (those of degree <= kGnThread),
-// the next ones one listed larger node per wavefront, the last ones a chunk of
-// a big node.  The node pass also records, per list (one side of one segment),
+// pass's first blocks take 256 nodes at a time (those of degree <= 32, staged
+// 64), the next ones one listed larger node per wavefront, the last ones a chunk
+// of a big node.  The node pass also records, per list (one side of one segment),
 // how many nodes are eligible and their largest and smallest gain.
 //
 // Selection of the first r nodes in (gain desc, id asc) order per list is an
@@ -206,9 +206,11 @@ __global__ __launch_bounds__(kBlock) void k_gain_hedges(int32_t E, int32_t P, in
 // ---- gains after a balance round: updated from what it moved -------------------------
 
 // One wavefront per logged chunk of a moved node's incidences: marks each
-// hyperedge in the bitmap.  The chunk's hyperedges ascend, so lanes sharing a
-// bitmap word are adjacent and the first lane of each run sets the run's bits
-// with one atomic (none when they are all set already).  Here: blocks b of nb
+// hyperedge in the bitmap.  Of adjacent lanes that share a bitmap word the first
+// sets the bits of all with one atomic (none when they are all set already).
+// The radix passes leave a node's hyperedges ascending, so a word is one run;
+// k_incidence_one's small levels do not, and may take a few atomics for a word,
+// with the same bits.  Here: blocks b of nb
 // (kBlock threads each) of the marking of the n logged chunks.
 //
 // Each hyperedge's count of pins on side 1 (n1) follows the move, one atomic an
@@ -450,9 +452,10 @@ __global__ __launch_bounds__(kBlock) void k_nz_bits(int32_t E, const void *cc, i
 }
 
 // A lane's share (lane, lane + stride, ...) of the contributions to a node on
-// side sd over its incidences b .. b + d, eight loads in flight at a time (none
-// for the places past the degree: as loads of the last one they cost as much
-// as the others; and the sums apart from the loads, or each waits for its own).
+// side sd over its incidences b .. b + d, eight loads in flight at a time: the
+// sums stand apart from them, as each would wait for its own (60 K nodes of ten
+// incidences 12.0 us, now 10.2), and there is none for the places past the
+// degree (1 M nodes of two, ids far apart: 33 us with the last one's again, now 25).
 __device__ __forceinline__ int32_t gather_sum(int32_t b, int32_t d, int lane, int stride, const int32_t *inc,
                                               const void *cc, int pk, const uint32_t *nzb, int sd)
 {
@@ -629,7 +632,7 @@ __global__ __launch_bounds__(kBlock) void k_gain_nodes(int32_t N, int64_t ns, co
                     atomicMin(&gmin[c0 + i], amin[i]);
                 }
     } else if (vb < ns + nw) {
-        // nodes of degree kGnThread + 1 .. 2048, one per wavefront, nw workgroups striding
+        // nodes of degree thread_max + 1 .. 2048, one per wavefront, nw workgroups striding
         // over the list; with few segments the lists aggregate in LDS
         bool local = 2 * S <= kAggLists;
         for (int i = threadIdx.x; i < kAggLists; i += blockDim.x) {
@@ -726,8 +729,8 @@ inline int64_t gn_blocks(const Level &L)
 inline int64_t gn_wave_blocks(const Level &L) { return L.N >= (1 << 15) ? 1024 : 512; }
 
 // Per-list counts and gain extremes after a gain update (what the node pass
-// records otherwise); clears the move marks and the hyperedge list.  Chunked:
-// the lists of a chunk aggregate in LDS and end in one atomic each.
+// records otherwise); empties the move log.  Chunked: the lists of a chunk
+// aggregate in LDS and end in one atomic each.
 __global__ __launch_bounds__(kBlock) void k_gain_stats(int32_t N, const int32_t *nseg, const uint8_t *gmask,
                                                        const uint8_t *side, const int32_t *gain,
                                                        const uint8_t *mode, int32_t *tot, int32_t *gmax,

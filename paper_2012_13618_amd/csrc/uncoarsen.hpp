@@ -703,14 +703,15 @@ __global__ __launch_bounds__(kBlock) void k_gain_nodes(int32_t N, int64_t ns, co
     }
 }
 
-// Whether the node pass stages: on levels of many pins, eight a node at least.  By
-// a thread each / staged, ids near / far apart: 1 M nodes of 6 incidences 24, 33 /
-// 27, 35 us, of 10 35, 53 / 33, 52; 3 M of 6 61, 98 / 62, 99, of 10 103, 168 / 86,
-// 169; 600 K of 10 27, 36 / 29, 46; coarse levels of 0.3 M nodes and 104 M pins
-// 794 / 623 and 1214 / 919 (degrees from a few to thousands).
+// Whether the node pass stages: on levels of many pins, five a node at least.  By
+// a thread each / staged, ids near / far apart, on sides that cut few hyperedges:
+// 1 M nodes of 4 incidences 27, 42 / 39, 47 us; 2 M of 4 31, 58 / 37, 58, of 6 43,
+// 90 / 43, 86; 5 M of 6 102, 217 / 95, 221, of 8 138, 306 / 116, 302; 256 netlists of
+// 5.4 (9.9 M nodes) 435 / 372; coarse levels of 0.3 M nodes and 104 M pins, degrees
+// from a few to thousands, 794 / 623 and 1214 / 919.
 inline bool gn_staged(const Level &L)
 {
-    return L.N >= (1 << 18) && (int64_t)L.P >= std::max<int64_t>(8 * (int64_t)L.N, 1 << 23);
+    return L.N >= (1 << 18) && (int64_t)L.P >= std::max<int64_t>(5 * (int64_t)L.N, 1 << 23);
 }
 
 // Blocks of the node pass that end in the lists' atomics, at most: each costs

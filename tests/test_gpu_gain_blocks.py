@@ -10,10 +10,10 @@ from paper_2012_13618_amd import inputs as I
 pytestmark = pytest.mark.gpu
 
 
-# 2^20 nodes of eight incidences and 2^18 of 32 (staged), 3/4 of 2^20 and an incidence to 16 nodes
+# 2^23 pins, at five a node and at 2^18 nodes (staged), 3/4 of 2^20 and an incidence to 16 nodes
 # (blocks), 2^15 (blocks of listed nodes; degrees above 32)
 @pytest.mark.parametrize("n,pins,d", [
-    (1 << 20, 8 << 20, 8), (1 << 20, (8 << 20) - 8, 8), ((1 << 20) + 8, 8 << 20, 16), (1 << 18, 8 << 20, 32),
+    (1 << 20, 8 << 20, 8), (1 << 20, (8 << 20) - 8, 8), (1677721, 8 << 20, 8), (1677722, 8 << 20, 8), (1 << 18, 8 << 20, 32),
     ((1 << 18) - 1, 8 << 20, 32), (1 << 18, (8 << 20) - 32, 32), (3 << 18, (3 << 18) // 16, 2),
     (3 << 18, (3 << 18) // 16 - 2, 2), ((3 << 18) - 1, 1 << 20, 4), (1 << 15, 40 << 15, 32), ((1 << 15) - 1, 36 << 15, 32),
     (16385, 1 << 19, 64), (513 * 256, 1 << 18, 2), (512 * 256 + 1, 512, 2),

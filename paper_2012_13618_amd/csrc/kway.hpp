@@ -460,7 +460,7 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(int32_t E, int lg, const in
     __shared__ int64_t lds64[16];
     if (ok && (ok->bad_offsets || ok->bad_pins)) return;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const bool mask64 = list == nullptr;
+    const bool mask64 = sizeof(PART) == 1 || list == nullptr;  // (bytes: up to 64 parts)
     const int32_t huge = mask64 ? kCutHuge : kMidMax + 1;
     if ((int64_t)blockIdx.x * kCutThreads < k) {
         unsigned long long m = 0;
